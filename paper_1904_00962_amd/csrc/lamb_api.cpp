@@ -49,14 +49,13 @@ struct lamb_plan {
     int32_t n_tiles = 0;
     int32_t n_rest = 0;            // layers outside the single pass
     int32_t n_rest_chunks = 0;
-    ChunkDesc *tiles = nullptr;
+    TileDesc *tiles = nullptr;     // the single pass's entries (tails at their offsets)
     uint64_t *slots = nullptr;     // 2 x 3 x n_tiles slot words
     uint32_t *ctl = nullptr;       // FusedCtl words
     // Layers of more than one round of tiles keep a head on the two-pass
     // kernels (rest_tensors) and put their tail on the single pass.
     TensorDesc *rest_tensors = nullptr;
     int32_t *rest_ids = nullptr;    // tensor id (in rest_tensors) of every fine chunk of the heads
-    TensorDesc *fused_tensors = nullptr;  // the single pass's table: tails at their offsets
     double *ext_totals = nullptr;   // the heads' partial-norm totals (2 per head, then a verdict)
     // Finalize segments of the fine, the coarse and the other-layers table.
     SegDesc *segs[3] = {};
@@ -66,7 +65,9 @@ struct lamb_plan {
     int fused_per_cu[4][2][3] = {};  // single-pass workgroups per CU by algo, bf16, norm
     std::vector<TensorDesc> host_tensors;  // host image of the tensor table
     std::vector<TensorDesc> host_rest;     // host image of the heads' table
-    std::vector<TensorDesc> host_fused;    // host image of the single pass's table
+    std::vector<TileDesc> host_tiles;      // host image of the tile list
+    std::vector<int32_t> tile_count;       // tiles of each layer on the single pass
+    std::vector<int32_t> first_tile;       // its first entry in the list
     std::vector<int64_t> single_elems;     // elements of each layer on the single pass
     std::vector<std::pair<uintptr_t, uintptr_t>> ranges;  // sorted buffer ranges of the table
     // finiteness check of skip_nonfinite steps that take the single pass
@@ -218,10 +219,10 @@ hipError_t gated_fused_launch(int device, hipStream_t stream, const StepKind &ki
     if (err != hipSuccess)
         return err;
     if (capture != hipStreamCaptureStatusNone)
-        return launch_fused(kind, plan->tile_groups, plan->fused_tensors, plan->tiles,
-                            plan->n_tiles, grid, plan->slots, plan->ctl, plan->flags, guarded,
-                            nonfinite_out, a, f, ratio_out, norms_out, plan->ext_totals,
-                            plan->scale, plan->trace, stream);
+        return launch_single_pass(kind, plan->tile_groups, plan->tiles, plan->n_tiles, grid,
+                                  plan->slots, plan->ctl, plan->flags, guarded, nonfinite_out,
+                                  a, f, ratio_out, norms_out, plan->ext_totals, plan->scale,
+                                  plan->trace, stream);
     std::lock_guard<std::mutex> lock(g_gate_mutex);
     if (g_gates.size() <= size_t(device))
         g_gates.resize(size_t(device) + 1);
@@ -239,9 +240,10 @@ hipError_t gated_fused_launch(int device, hipStream_t stream, const StepKind &ki
         if (err != hipSuccess)
             return err;
     }
-    err = launch_fused(kind, plan->tile_groups, plan->fused_tensors, plan->tiles, plan->n_tiles,
-                       grid, plan->slots, plan->ctl, plan->flags, guarded, nonfinite_out, a, f,
-                       ratio_out, norms_out, plan->ext_totals, plan->scale, plan->trace, stream);
+    err = launch_single_pass(kind, plan->tile_groups, plan->tiles, plan->n_tiles, grid,
+                             plan->slots, plan->ctl, plan->flags, guarded, nonfinite_out, a, f,
+                             ratio_out, norms_out, plan->ext_totals, plan->scale, plan->trace,
+                             stream);
     if (err != hipSuccess)
         return err;
     err = hipEventRecord(gate.done, stream);
@@ -696,13 +698,10 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
                                 nullptr);
     if (st != LAMB_OK)
         return st;
-    std::vector<ChunkDesc> host_tiles(static_cast<size_t>(n_entries));
-    for (int32_t k = 0; k < n_entries; ++k)
-        host_tiles[size_t(k)] =
-            ChunkDesc{entry_tensor[size_t(k)], entry_len[size_t(k)], entry_start[size_t(k)]};
-    // Three tensor tables: every layer whole (the two-pass path and the split
-    // step), the single pass's (tails at their offsets), and the heads.
-    std::vector<TensorDesc> host_fused(static_cast<size_t>(n_tensors));
+    // Two tensor tables, every layer whole (the two-pass path and the split
+    // step) and the heads, and the single pass's tile list (tails at their
+    // offsets; empty entries stay zero).
+    std::vector<TileDesc> host_tiles(static_cast<size_t>(n_entries), TileDesc{});
     std::vector<TensorDesc> host_rest;
     std::vector<int32_t> host_rest_ids;
     {
@@ -711,33 +710,44 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
             const lamb_tensor &t = tensors[i];
             const int32_t nc = int32_t((t.numel + chunk - 1) / chunk);
             const int32_t ncc = int32_t((t.numel + coarse - 1) / coarse);
-            TensorDesc d{t.x,          t.g,          t.m,   needs_v ? t.v : nullptr,
-                         nullptr,      t.numel,      t.wd,  first,
-                         nc,           first_coarse, ncc,   first_tile[size_t(i)],
-                         tile_count[size_t(i)], i,   -1};
+            TensorDesc d{t.x,     t.g,  t.m,   needs_v ? t.v : nullptr,
+                         nullptr, t.numel, t.wd, first,
+                         first_coarse, i,  {}};
             host_tensors[size_t(i)] = d;
             const int64_t h = head[size_t(i)];
-            TensorDesc f = d;
-            f.first_chunk = f.n_chunks = f.first_coarse = f.n_coarse = 0;
+            int32_t ext = -1;
             if (h > 0) {
-                const size_t g_size = g_dtype == LAMB_GRAD_BF16 ? 2 : 4;
-                f.x = t.x + h;
-                f.g = static_cast<const char *>(t.g) + h * int64_t(g_size);
-                f.m = t.m + h;
-                f.v = needs_v ? t.v + h : nullptr;
-                f.numel = tail[size_t(i)];
-                f.ext = int32_t(host_rest.size());
+                ext = int32_t(host_rest.size());
                 TensorDesc r = d;
                 r.numel = h;
                 r.first_chunk = int32_t(host_rest_ids.size());
-                r.n_chunks = int32_t((h + chunk - 1) / chunk);
-                r.first_coarse = r.n_coarse = 0;
-                r.first_tile = r.n_tiles = 0;
-                for (int32_t k = 0; k < r.n_chunks; ++k)
-                    host_rest_ids.push_back(f.ext);
+                r.first_coarse = 0;
+                host_rest_ids.resize(host_rest_ids.size() + size_t((h + chunk - 1) / chunk), ext);
                 host_rest.push_back(r);
             }
-            host_fused[size_t(i)] = f;
+            const size_t g_size = g_dtype == LAMB_GRAD_BF16 ? 2 : 4;
+            TileDesc td{t.x + h,
+                        static_cast<const char *>(t.g) + h * int64_t(g_size),
+                        t.m + h,
+                        needs_v ? t.v + h : nullptr,
+                        nullptr,
+                        int32_t(tail[size_t(i)]),
+                        0,
+                        tile_count[size_t(i)],
+                        i,
+                        ext,
+                        0};
+            // blocks that hold any whole float4, and the last block of all,
+            // ragged when the layer ends inside it
+            const int32_t blocks = (td.numel / 4 * 4 + kBlockElems - 1) / kBlockElems;
+            const int32_t last = (td.numel - 1) / kBlockElems;
+            for (int32_t k = 0; k < td.n_tiles; ++k) {
+                td.index = k;
+                td.shape = tile_shape(
+                    t.wd != 0, td.numel % kBlockElems != 0 && last % td.n_tiles == k,
+                    k < blocks ? (blocks - k + td.n_tiles - 1) / td.n_tiles : 0);
+                host_tiles[size_t(first_tile[size_t(i)]) + size_t(k)] = td;
+            }
             first += nc;
             first_coarse += ncc;
         }
@@ -749,12 +759,15 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
     std::vector<SegRange> host_ranges[3];
     {
         std::vector<std::pair<int32_t, int32_t>> fine, coarse_tc, rest;
+        auto chunks = [](const TensorDesc &d, int32_t elems) {
+            return int32_t((d.numel + elems - 1) / elems);
+        };
         for (const TensorDesc &d : host_tensors) {
-            fine.emplace_back(d.first_chunk, d.n_chunks);
-            coarse_tc.emplace_back(d.first_coarse, d.n_coarse);
+            fine.emplace_back(d.first_chunk, chunks(d, chunk));
+            coarse_tc.emplace_back(d.first_coarse, chunks(d, coarse));
         }
         for (const TensorDesc &d : host_rest)
-            rest.emplace_back(d.first_chunk, d.n_chunks);
+            rest.emplace_back(d.first_chunk, chunks(d, chunk));
         build_segments(fine, &host_segs[kSegFine], &host_ranges[kSegFine]);
         build_segments(coarse_tc, &host_segs[kSegCoarse], &host_ranges[kSegCoarse]);
         build_segments(rest, &host_segs[kSegRest], &host_ranges[kSegRest]);
@@ -778,12 +791,11 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
     const size_t partial_bytes = round256(sizeof(Partial) * size_t(n_chunks));
     const size_t scale_bytes = round256(sizeof(float) * size_t(n_tensors));
     const size_t flag_bytes = 256;
-    const size_t tiles_bytes = round256(sizeof(ChunkDesc) * size_t(n_tiles));
+    const size_t tiles_bytes = round256(sizeof(TileDesc) * size_t(n_tiles));
     const size_t slot_bytes = round256(sizeof(uint64_t) * 6 * size_t(n_tiles));
     const size_t ctl_bytes = 256;
     const size_t rest_bytes = round256(sizeof(TensorDesc) * size_t(n_rest));
     const size_t rest_chunk_bytes = round256(sizeof(int32_t) * size_t(n_rest_chunks));
-    const size_t fused_bytes = round256(sizeof(TensorDesc) * size_t(n_tensors));
     const size_t ext_bytes = round256(sizeof(double) * (2 * size_t(n_rest) + 1));
     size_t seg_bytes[3], range_bytes[3];
     for (int k = 0; k < 3; ++k) {
@@ -795,7 +807,7 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
     err = hipMalloc(&plan->device_block,
                     tensors_bytes + chunks_bytes + coarse_bytes + partial_bytes + scale_bytes +
                         flag_bytes + tiles_bytes + slot_bytes + ctl_bytes + rest_bytes +
-                        rest_chunk_bytes + fused_bytes + ext_bytes + seg_bytes[0] +
+                        rest_chunk_bytes + ext_bytes + seg_bytes[0] +
                         seg_bytes[1] + seg_bytes[2] +
                         range_bytes[0] + range_bytes[1] + range_bytes[2] + seg_partial_bytes +
                         check_bytes);
@@ -818,7 +830,7 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
     base += scale_bytes;
     plan->flags = reinterpret_cast<uint32_t *>(base);
     base += flag_bytes;
-    plan->tiles = reinterpret_cast<ChunkDesc *>(base);
+    plan->tiles = reinterpret_cast<TileDesc *>(base);
     base += tiles_bytes;
     plan->slots = reinterpret_cast<uint64_t *>(base);
     base += slot_bytes;
@@ -828,8 +840,6 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
     base += rest_bytes;
     plan->rest_ids = reinterpret_cast<int32_t *>(base);
     base += rest_chunk_bytes;
-    plan->fused_tensors = reinterpret_cast<TensorDesc *>(base);
-    base += fused_bytes;
     plan->ext_totals = reinterpret_cast<double *>(base);
     base += ext_bytes;
     for (int k = 0; k < 3; ++k) {
@@ -852,7 +862,7 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
         err = hipMemcpy(plan->coarse_ids, ids_of(host_coarse).data(),
                         sizeof(int32_t) * size_t(n_coarse), hipMemcpyHostToDevice);
     if (err == hipSuccess && n_tiles > 0)
-        err = hipMemcpy(plan->tiles, host_tiles.data(), sizeof(ChunkDesc) * size_t(n_tiles),
+        err = hipMemcpy(plan->tiles, host_tiles.data(), sizeof(TileDesc) * size_t(n_tiles),
                         hipMemcpyHostToDevice);
     if (err == hipSuccess && n_rest > 0)
         err = hipMemcpy(plan->rest_tensors, host_rest.data(), sizeof(TensorDesc) * size_t(n_rest),
@@ -860,9 +870,6 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
     if (err == hipSuccess && n_rest > 0)
         err = hipMemcpy(plan->rest_ids, host_rest_ids.data(),
                         sizeof(int32_t) * size_t(n_rest_chunks), hipMemcpyHostToDevice);
-    if (err == hipSuccess)
-        err = hipMemcpy(plan->fused_tensors, host_fused.data(),
-                        sizeof(TensorDesc) * size_t(n_tensors), hipMemcpyHostToDevice);
     for (int k = 0; k < 3 && err == hipSuccess; ++k) {
         if (!host_segs[k].empty())
             err = hipMemcpy(plan->segs[k], host_segs[k].data(),
@@ -919,7 +926,9 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
     plan->n_rest = n_rest;
     plan->n_rest_chunks = n_rest_chunks;
     plan->host_tensors = std::move(host_tensors);
-    plan->host_fused = std::move(host_fused);
+    plan->host_tiles = std::move(host_tiles);
+    plan->tile_count = std::move(tile_count);
+    plan->first_tile = std::move(first_tile);
     plan->host_rest = std::move(host_rest);
     plan->single_elems = std::move(tail);
     for (const BufferRange &r : ranges)
@@ -1306,21 +1315,23 @@ lamb_status lamb_plan_set_bf16_copies(lamb_plan *plan, void *const *copies) {
     std::vector<TensorDesc> next_rest = plan->host_rest;
     for (TensorDesc &r : next_rest)
         r.x_copy = next[size_t(r.out_index)].x_copy;
-    // the single pass's table holds the tails of split layers at an offset
-    std::vector<TensorDesc> next_fused = plan->host_fused;
+    // the single pass's tiles hold the tails of split layers at an offset
+    std::vector<TileDesc> next_tiles = plan->host_tiles;
     for (int32_t i = 0; i < plan->n_tensors; ++i) {
         uint16_t *c = next[size_t(i)].x_copy;
-        const int64_t head = next[size_t(i)].numel - next_fused[size_t(i)].numel;
-        next_fused[size_t(i)].x_copy = c ? c + head : nullptr;
+        if (c)
+            c += next[size_t(i)].numel - plan->single_elems[size_t(i)];
+        for (int32_t k = 0; k < plan->tile_count[size_t(i)]; ++k)
+            next_tiles[size_t(plan->first_tile[size_t(i)]) + size_t(k)].x_copy = c;
     }
     DeviceGuard guard(plan->device);
     if (guard.status != hipSuccess)
         return fail_hip(guard.status, "selecting the plan's device");
     hipError_t err = hipMemcpy(plan->tensors, next.data(),
                                sizeof(TensorDesc) * size_t(plan->n_tensors), hipMemcpyHostToDevice);
-    if (err == hipSuccess)
-        err = hipMemcpy(plan->fused_tensors, next_fused.data(),
-                        sizeof(TensorDesc) * size_t(plan->n_tensors), hipMemcpyHostToDevice);
+    if (err == hipSuccess && plan->n_tiles > 0)
+        err = hipMemcpy(plan->tiles, next_tiles.data(), sizeof(TileDesc) * next_tiles.size(),
+                        hipMemcpyHostToDevice);
     if (err == hipSuccess && plan->n_rest > 0)
         err = hipMemcpy(plan->rest_tensors, next_rest.data(),
                         sizeof(TensorDesc) * size_t(plan->n_rest), hipMemcpyHostToDevice);
@@ -1329,7 +1340,7 @@ lamb_status lamb_plan_set_bf16_copies(lamb_plan *plan, void *const *copies) {
     if (err != hipSuccess)
         return fail_hip(err, "hipMemcpy of the tensor table");
     plan->host_tensors = std::move(next);
-    plan->host_fused = std::move(next_fused);
+    plan->host_tiles = std::move(next_tiles);
     plan->host_rest = std::move(next_rest);
     return LAMB_OK;
 }
@@ -1349,7 +1360,7 @@ lamb_status lamb_plan_tiles(const lamb_plan *plan, int32_t *tiles_per_tensor, in
         return fail(LAMB_ENULL, "plan must not be NULL");
     if (tiles_per_tensor)
         for (int32_t i = 0; i < plan->n_tensors; ++i)
-            tiles_per_tensor[i] = plan->host_fused[size_t(i)].n_tiles;
+            tiles_per_tensor[i] = plan->tile_count[size_t(i)];
     if (single_elems)
         for (int32_t i = 0; i < plan->n_tensors; ++i)
             single_elems[i] = plan->single_elems[size_t(i)];

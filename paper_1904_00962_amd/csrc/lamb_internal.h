@@ -48,6 +48,13 @@ constexpr int32_t kBlockElems = kBlock * 4;  // one float4 per thread
 constexpr int64_t tile_elems(int groups) { return int64_t(groups) * kBlockElems; }
 constexpr int kFusedWaves = 4;  // waves per SIMD
 constexpr int kFusedBlocksPerCu = kFusedWaves * 4 / kWaves;  // 4 SIMDs per CU
+// A plan of at most this many rounds of tiles takes quick_kernel, a longer one
+// fused_kernel (lamb_kernels.hip says what differs). Measured against each
+// other on one GPU, quick_kernel's step: ragged lists of 0.3 to 8M elements
+// 12-18% to 4% faster, ResNet-50 5% (4 rounds), BERT shapes of 15M, 45M and 70M
+// parameters 2% each (3 to 9 rounds), BERT-Base 0.8% slower (fp32, 11 rounds),
+// GPT shapes of 120M and 1.5B 1.1-3% slower, BERT-Large 2.4% slower (37 rounds).
+constexpr int32_t kQuickRounds = 10;
 // Polls before a single-pass wait gives up (about a second); a plan reads an
 // override from the environment variable LAMB_MI355X_SPIN_LIMIT.
 constexpr uint32_t kDefaultSpinLimit = 1u << 22;
@@ -59,7 +66,7 @@ enum FusedCtl : int {
     kCtlFault = 2,  // sticky: a wait ran out of time and the step was abandoned
 };
 
-// One layer block x^(i) (Section 2) as the kernels see it. 80 bytes.
+// One layer block x^(i) (Section 2) as the two-pass kernels see it.
 struct TensorDesc {
     float *x;
     const void *g;
@@ -68,16 +75,13 @@ struct TensorDesc {
     uint16_t *x_copy;      // bf16 working copy written by the apply pass, or null
     int64_t numel;
     int32_t wd;            // 1: lambda applies, 0: lambda = 0
-    int32_t first_chunk;   // fine chunks [first_chunk, first_chunk + n_chunks)
-    int32_t n_chunks;
-    int32_t first_coarse;  // coarse chunks [first_coarse, first_coarse + n_coarse)
-    int32_t n_coarse;
-    int32_t first_tile;    // single-pass tiles [first_tile, first_tile + n_tiles);
-    int32_t n_tiles;       //   n_tiles = 0: the layer takes the two-pass path
+    int32_t first_chunk;   // its first fine chunk
+    int32_t first_coarse;  // its first coarse chunk
     int32_t out_index;     // the layer's index in ratio_out / norms_out
-    int32_t ext;           // single-pass table: the index of the layer's head in the
-                           // two-pass table (its partial-norm totals and its step
-                           // scale), or -1 when the whole layer is in the tiles
+    // Padding: with a stride of 64 or 72 bytes the two-pass BERT-Base step was
+    // 0.5% slower (702.3 -> 705.6 us), with 128 bytes the split step of
+    // BERT-Large's 1/8 share 0.9% (255.3 -> 257.7 us).
+    int32_t reserved[6];
 };
 static_assert(sizeof(TensorDesc) == 88, "TensorDesc layout");
 
@@ -88,6 +92,34 @@ struct ChunkDesc {
     int64_t start;
 };
 static_assert(sizeof(ChunkDesc) == 16, "ChunkDesc layout");
+
+// One tile of the single pass and everything its workgroup needs of its layer
+// (of the layer's tail, when a head of it takes the two-pass kernels), in one
+// 64-byte load. An empty entry that pads a round is all zeros.
+struct TileDesc {
+    float *x;
+    const void *g;
+    float *m;
+    float *v;          // null for LARS plans
+    uint16_t *x_copy;  // bf16 working copy, or null
+    int32_t numel;     // the layer's elements on the single pass, below 2^29
+    int32_t index;     // the tile's index in the layer
+    int32_t n_tiles;   // the layer's tiles, consecutive entries; 0: an empty entry
+    int32_t out_index; // the layer's index in ratio_out / norms_out
+    int32_t ext;       // the layer's head (its totals and step scale), or -1
+    // tile_shape(): one 32-bit word, which a scalar load can read
+    uint32_t shape;
+};
+static_assert(sizeof(TileDesc) == 64, "TileDesc layout");
+
+// TileDesc::shape: bit 0 lambda applies; bit 1 the tile holds the layer's last
+// block, and that is partial; above, its groups that hold any of the layer's
+// whole float4s.
+constexpr uint32_t kTileWd = 1, kTileRagged = 2, kTileGroupsShift = 2;
+constexpr uint32_t tile_shape(bool wd, bool ragged, int32_t groups) {
+    return (wd ? kTileWd : 0u) | (ragged ? kTileRagged : 0u) |
+           uint32_t(groups) << kTileGroupsShift;
+}
 
 // The finalize runs in two levels: a segment kernel folds each run of up to
 // kSegChunks consecutive chunk partials of one tensor into one segment
@@ -252,14 +284,17 @@ constexpr uint64_t kEmptySlot = ~uint64_t(0);
 // round) combines the totals of its head, ext_totals[2 ext] and
 // ext_totals[2 ext + 1], before its own tiles' partials, and writes its step
 // scale to ext_scale[ext] for the apply pass over the head.
-hipError_t launch_fused(const StepKind &kind, int groups, const TensorDesc *tensors,
-                        const ChunkDesc *tiles, int32_t n_tiles, int32_t grid, uint64_t *slots,
-                        uint32_t *ctl, uint32_t *flags, bool guarded, int32_t *nonfinite_out,
-                        const StepArgs &args, const FinalizeArgs &fargs, double *ratio_out,
-                        double *norms_out, const double *ext_totals, float *ext_scale,
-                        uint64_t *trace, hipStream_t stream);
-// Workgroups of the single-pass kernel for `kind` and tile shape `groups`
-// that fit on one CU at once.
+// Weak: a host-only build of lamb_api.cpp (a sanitizer run of its validation)
+// leaves the kernels out.
+hipError_t launch_single_pass(const StepKind &kind, int groups, const TileDesc *tiles,
+                              int32_t n_tiles, int32_t grid, uint64_t *slots, uint32_t *ctl,
+                              uint32_t *flags, bool guarded, int32_t *nonfinite_out,
+                              const StepArgs &args, const FinalizeArgs &fargs,
+                              double *ratio_out, double *norms_out, const double *ext_totals,
+                              float *ext_scale, uint64_t *trace, hipStream_t stream)
+    __attribute__((weak));
+// Workgroups of the single-pass kernels for `kind` and tile shape `groups`
+// that fit on one CU at once (the fewer of the two kernels').
 hipError_t fused_blocks_per_cu(const StepKind &kind, int groups, int *blocks);
 
 }  // namespace lamb_mi355x

@@ -145,13 +145,8 @@ __global__ __launch_bounds__(kBlock) void table_kernel(TableBatch b, StaticTable
         d.numel = r.numel;
         d.wd = r.wd;
         d.first_chunk = r.first_chunk;
-        d.n_chunks = nc;
         d.first_coarse = r.first_coarse;
-        d.n_coarse = ncc;
-        d.first_tile = 0;
-        d.n_tiles = 0;
         d.out_index = i;
-        d.ext = -1;
         t.tensors[i] = d;
         t.ranges[0][i] = SegRange{r.first_seg, ns};
         t.ranges[1][i] = SegRange{r.first_cseg, ncs};
