@@ -61,6 +61,7 @@ struct lamb_plan {
     SegDesc *segs[3] = {};
     SegRange *seg_ranges[3] = {};
     int32_t n_segs[3] = {};
+    bool direct_segs[3] = {};  // no tensor has more than kDirectSegs segments
     Partial *seg_partials = nullptr;
     int fused_per_cu[4][2][3] = {};  // single-pass workgroups per CU by algo, bf16, norm
     std::vector<TensorDesc> host_tensors;  // host image of the tensor table
@@ -552,17 +553,37 @@ std::vector<int32_t> ids_of(const std::vector<ChunkDesc> &chunks) {
 }
 
 // Finalize segments of a chunk table: tensor k's chunk partials
-// [first_k, first_k + count_k) cut into runs of kSegChunks.
-void build_segments(const std::vector<std::pair<int32_t, int32_t>> &tensor_chunks,
+// [first_k, first_k + count_k) cut into runs of kSegChunks. Returns whether the
+// table finalizes in one kernel: `segs` is empty then, and `ranges` are the
+// tensors' chunk spans.
+bool build_segments(const std::vector<std::pair<int32_t, int32_t>> &tensor_chunks,
                     std::vector<SegDesc> *segs, std::vector<SegRange> *ranges) {
     segs->clear();
     ranges->clear();
+    if (std::all_of(tensor_chunks.begin(), tensor_chunks.end(),
+                    [](const auto &tc) { return tc.second <= kDirectSegs * kSegChunks; })) {
+        for (const auto &tc : tensor_chunks)
+            ranges->push_back(SegRange{tc.first, tc.second});
+        return true;
+    }
     for (const auto &tc : tensor_chunks) {
         const int32_t first_seg = int32_t(segs->size());
         for (int32_t k = 0; k < tc.second; k += kSegChunks)
             segs->push_back(SegDesc{tc.first + k, std::min(kSegChunks, tc.second - k)});
         ranges->push_back(SegRange{first_seg, int32_t(segs->size()) - first_seg});
     }
+    return false;
+}
+
+// The totals of the `n` tensors of segment table `seg`.
+hipError_t plan_totals(const lamb_plan *plan, int seg, NormKind norm, int32_t n, double *totals,
+                       VerdictMode verdict, hipStream_t s) {
+    if (plan->direct_segs[seg])
+        return launch_direct_totals(norm, plan->partials, plan->seg_ranges[seg], n, totals,
+                                    plan->flags, plan->ctl, verdict, s);
+    return launch_totals(norm, plan->partials, plan->segs[seg], plan->n_segs[seg],
+                         plan->seg_ranges[seg], n, plan->seg_partials, totals, plan->flags,
+                         plan->ctl, verdict, s);
 }
 
 }  // namespace lamb_mi355x
@@ -757,6 +778,7 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
     const int32_t n_rest_chunks = int32_t(host_rest_ids.size());
     std::vector<SegDesc> host_segs[3];
     std::vector<SegRange> host_ranges[3];
+    bool direct_segs[3];
     {
         std::vector<std::pair<int32_t, int32_t>> fine, coarse_tc, rest;
         auto chunks = [](const TensorDesc &d, int32_t elems) {
@@ -768,9 +790,12 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
         }
         for (const TensorDesc &d : host_rest)
             rest.emplace_back(d.first_chunk, chunks(d, chunk));
-        build_segments(fine, &host_segs[kSegFine], &host_ranges[kSegFine]);
-        build_segments(coarse_tc, &host_segs[kSegCoarse], &host_ranges[kSegCoarse]);
-        build_segments(rest, &host_segs[kSegRest], &host_ranges[kSegRest]);
+        direct_segs[kSegFine] =
+            build_segments(fine, &host_segs[kSegFine], &host_ranges[kSegFine]);
+        direct_segs[kSegCoarse] =
+            build_segments(coarse_tc, &host_segs[kSegCoarse], &host_ranges[kSegCoarse]);
+        direct_segs[kSegRest] =
+            build_segments(rest, &host_segs[kSegRest], &host_ranges[kSegRest]);
     }
     size_t max_segs = 1;
     for (const auto &v : host_segs)
@@ -848,6 +873,7 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
         plan->seg_ranges[k] = reinterpret_cast<SegRange *>(base);
         base += range_bytes[k];
         plan->n_segs[k] = int32_t(host_segs[k].size());
+        plan->direct_segs[k] = direct_segs[k];
     }
     plan->seg_partials = reinterpret_cast<Partial *>(base);
     base += seg_partial_bytes;
@@ -1182,10 +1208,8 @@ lamb_status lamb_step_ex(lamb_plan *plan, const lamb_hparams *hp, void *stream,
             if (err != hipSuccess)
                 return fail_hip(err, "launching the moment kernel");
             mark(plan, kTimedMoments, s);
-            err = launch_totals(direct.norm, plan->partials, plan->segs[kSegRest],
-                                plan->n_segs[kSegRest], plan->seg_ranges[kSegRest], plan->n_rest,
-                                plan->seg_partials, plan->ext_totals, plan->flags, plan->ctl,
-                                checked ? kVerdictCopy : kVerdictZero, s);
+            err = plan_totals(plan, kSegRest, direct.norm, plan->n_rest, plan->ext_totals,
+                              checked ? kVerdictCopy : kVerdictZero, s);
             if (err != hipSuccess)
                 return fail_hip(err, "launching the totals kernel");
             mark(plan, kTimedFinalize, s);
@@ -1218,10 +1242,16 @@ lamb_status lamb_step_ex(lamb_plan *plan, const lamb_hparams *hp, void *stream,
             return fail_hip(err, "launching the moment kernel");
         mark(plan, kTimedMoments, s);
         const int seg = kind.deferred ? kSegCoarse : kSegFine;
-        err = launch_finalize(kind.norm, plan->tensors, plan->n_tensors, plan->partials,
-                              plan->segs[seg], plan->n_segs[seg], plan->seg_ranges[seg],
-                              plan->seg_partials, f, plan->scale, ratio_out, norms_out,
-                              kind.deferred ? plan->flags : nullptr, s);
+        uint32_t *flags = kind.deferred ? plan->flags : nullptr;
+        if (plan->direct_segs[seg])
+            err = launch_direct_finalize(kind.norm, plan->tensors, plan->n_tensors,
+                                         plan->partials, plan->seg_ranges[seg], f, plan->scale,
+                                         ratio_out, norms_out, flags, s);
+        else
+            err = launch_finalize(kind.norm, plan->tensors, plan->n_tensors, plan->partials,
+                                  plan->segs[seg], plan->n_segs[seg], plan->seg_ranges[seg],
+                                  plan->seg_partials, f, plan->scale, ratio_out, norms_out, flags,
+                                  s);
         if (err != hipSuccess)
             return fail_hip(err, "launching the finalize kernel");
         mark(plan, kTimedFinalize, s);
@@ -1519,9 +1549,8 @@ lamb_status lamb_step_partials(lamb_plan *plan, const lamb_hparams *hp, void *st
     if (err != hipSuccess)
         return fail_hip(err, "launching the moment kernel");
     const int seg = kind.deferred ? kSegCoarse : kSegFine;
-    err = launch_totals(kind.norm, plan->partials, plan->segs[seg], plan->n_segs[seg],
-                        plan->seg_ranges[seg], plan->n_tensors, plan->seg_partials, totals,
-                        plan->flags, plan->ctl, kind.deferred ? kVerdictMove : kVerdictZero, s);
+    err = plan_totals(plan, seg, kind.norm, plan->n_tensors, totals,
+                      kind.deferred ? kVerdictMove : kVerdictZero, s);
     if (err != hipSuccess)
         return fail_hip(err, "launching the totals kernel");
     plan->u_check_chunks = 0;

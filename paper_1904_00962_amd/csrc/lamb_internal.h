@@ -121,10 +121,9 @@ constexpr uint32_t tile_shape(bool wd, bool ragged, int32_t groups) {
            uint32_t(groups) << kTileGroupsShift;
 }
 
-// The finalize runs in two levels: a segment kernel folds each run of up to
-// kSegChunks consecutive chunk partials of one tensor into one segment
-// partial, then the per-tensor finalize combines the tensor's segment
-// partials. Both in a fixed order.
+// The finalize has two levels: each run of up to kSegChunks consecutive chunk
+// partials of one tensor is folded into one segment partial, then the tensor's
+// segment partials are combined. Both in a fixed order.
 constexpr int kSegBlock = 256;
 constexpr int kSegLanes = 8;
 constexpr int32_t kSegChunks = kSegBlock * kSegLanes;
@@ -135,11 +134,19 @@ struct SegDesc {
     int32_t count;
 };
 
-// A tensor's segments: [first, first + count) of the segment list.
+// A tensor's segments: [first, first + count) of the segment list; in a table
+// that finalizes in one kernel, its span of the chunk partials.
 struct SegRange {
     int32_t first;
     int32_t count;
 };
+
+// Tables whose widest tensor has at most kDirectSegs segments (8.4M elements
+// in 256-element chunks) finalize in one kernel of kDirectBlock threads per
+// tensor instead of two kernels.
+constexpr int kDirectBlock = 4 * kSegBlock;
+constexpr int32_t kDirectSegs = 16;
+static_assert(kDirectSegs <= 64, "one wave combines the segments' totals");
 
 // Per-chunk partial norms of x and of the update direction u (LAMB family)
 // or m_t (LARS), written once per step at a fixed slot: sums of squares (L2),
@@ -233,6 +240,14 @@ hipError_t launch_finalize(NormKind norm, const TensorDesc *tensors, int32_t n_t
                            const SegRange *ranges, Partial *seg_partials,
                            const FinalizeArgs &args, float *scale, double *ratio_out,
                            double *norms_out, uint32_t *flags, hipStream_t stream);
+// The same in one kernel, for a table whose tensors have at most kDirectSegs
+// segments each (the caller checks); `spans`: every tensor's chunk partials.
+// Weak, as launch_single_pass below.
+hipError_t launch_direct_finalize(NormKind norm, const TensorDesc *tensors, int32_t n_tensors,
+                                  const Partial *partials, const SegRange *spans,
+                                  const FinalizeArgs &args, float *scale, double *ratio_out,
+                                  double *norms_out, uint32_t *flags, hipStream_t stream)
+    __attribute__((weak));
 // `check` non-null (direct mode only): also re-sum the partial norms of every
 // chunk from the x read and the u recomputed, into check[chunk].
 hipError_t launch_apply(const StepKind &kind, const TensorDesc *tensors,
@@ -254,6 +269,11 @@ hipError_t launch_totals(NormKind norm, const Partial *partials, const SegDesc *
                          int32_t n_segs, const SegRange *ranges, int32_t n_tensors,
                          Partial *seg_partials, double *totals, uint32_t *flags,
                          const uint32_t *ctl, int32_t verdict_mode, hipStream_t stream);
+// The same in one kernel, as launch_direct_finalize.
+hipError_t launch_direct_totals(NormKind norm, const Partial *partials, const SegRange *spans,
+                                int32_t n_tensors, double *totals, uint32_t *flags,
+                                const uint32_t *ctl, int32_t verdict_mode, hipStream_t stream)
+    __attribute__((weak));
 // Split step, second half: per tensor the norms, phi, ratio and scale from
 // combined totals; flags[1] receives the combined verdict for a deferred
 // apply pass.

@@ -680,64 +680,130 @@ __global__ __launch_bounds__(kBlock) void finite_kernel(const TensorDesc *__rest
 }
 
 // ---------------------------------------------------------------------------
-// Finalize, in two levels. The segment kernel gives each workgroup up to
-// kSegChunks consecutive chunk partials of one tensor: thread k folds slots
+// Finalize, in two levels: each segment of up to kSegChunks consecutive chunk
+// partials of one tensor is folded by 256 threads, thread k taking slots
 // k + j * kSegBlock into kSegLanes independent accumulators (several loads in
-// flight), combines them in a fixed order, and the fixed wave/LDS tree
-// combines the threads into the segment's partial. The per-tensor finalize
-// then combines the tensor's segment partials the same way and forms the
-// norms, phi, trust ratio and step scale. The order never depends on timing.
+// flight), combined in a fixed order and by the fixed wave/LDS tree; then the
+// tensor's segment partials are combined the same way into the norms, phi,
+// trust ratio and step scale. The order never depends on timing.
+//
+// Both levels run in one kernel (kDirectBlock threads a tensor, eight segments
+// in flight) when no tensor of the table has more than kDirectSegs segments,
+// and in two kernels otherwise, same bits either way. The levels take no
+// bandwidth to speak of: they cost their launches and dependent loads.
+// Of BERT-Large's 1/8 share (up to 8 segments a tensor) one kernel takes 6.2 us,
+// two took 9.5, and the split step went 257.3 -> 253.9 us; ResNet-50's planless
+// step 5.2 against 9 us. Tensors of many segments (a 23M-element embedding: 45)
+// are faster spread over workgroups.
 // ---------------------------------------------------------------------------
+
+// A thread's share of one segment's partials: slots k0 + j * kSegBlock of the
+// `count` from `p` on (a count of 0 or less: no segment).
+struct SegmentShare {
+    Partial q[kSegLanes];
+    __device__ __forceinline__ void load(const Partial *__restrict__ p, int32_t count, int k0) {
+#pragma unroll
+        for (int j = 0; j < kSegLanes; ++j) {
+            const int k = k0 + j * kSegBlock;
+            q[j] = k < count ? p[k] : Partial{0.0, 0.0};
+        }
+    }
+    template <int kNorm>
+    __device__ __forceinline__ Partial combine() const {
+        Partial t = q[0];
+#pragma unroll
+        for (int j = 1; j < kSegLanes; ++j) {
+            t.sum_xx = norm_combine<kNorm>(t.sum_xx, q[j].sum_xx);
+            t.sum_uu = norm_combine<kNorm>(t.sum_uu, q[j].sum_uu);
+        }
+        return t;
+    }
+};
 
 template <int kNorm>
 __global__ __launch_bounds__(kSegBlock) void segment_kernel(const Partial *__restrict__ partials,
                                                           const SegDesc *__restrict__ segs,
                                                           Partial *__restrict__ seg_partials) {
     const SegDesc sd = segs[blockIdx.x];
-    const Partial *p = partials + sd.first;
-    double sx[kSegLanes] = {}, su[kSegLanes] = {};
-#pragma unroll
-    for (int j = 0; j < kSegLanes; ++j) {
-        const int k = threadIdx.x + j * kSegBlock;
-        if (k < sd.count) {
-            const Partial q = p[k];
-            sx[j] = q.sum_xx;
-            su[j] = q.sum_uu;
-        }
-    }
-#pragma unroll
-    for (int j = 1; j < kSegLanes; ++j) {
-        sx[0] = norm_combine<kNorm>(sx[0], sx[j]);
-        su[0] = norm_combine<kNorm>(su[0], su[j]);
-    }
-    block_combine<kNorm, kSegBlock / 64>(sx[0], su[0], seg_partials + blockIdx.x);
+    SegmentShare share;
+    share.load(partials + sd.first, sd.count, int(threadIdx.x));
+    const Partial q = share.combine<kNorm>();
+    block_combine<kNorm, kSegBlock / 64>(q.sum_xx, q.sum_uu, seg_partials + blockIdx.x);
 }
 
-// A tensor's combined partial norms from its segment partials, in a fixed
-// order (every thread of the workgroup returns it).
+// A tensor's combined partial norms in a fixed order, in thread 0: from its
+// segment partials, range `r` (kSegBlock threads), or, `direct`, from its chunk
+// partials, range `r` (kDirectBlock threads): waves 4 q .. 4 q + 3 fold
+// segments q, q + 4, ..., two at a time so that one latency covers both (one at
+// a time for L-infinity), and wave 0 combines the (at most kDirectSegs)
+// segments' totals.
 template <int kNorm>
-__device__ Partial tensor_total(const Partial *__restrict__ seg_partials, SegRange r) {
-    double sx = 0.0, su = 0.0;
-    for (int k = threadIdx.x; k < r.count; k += kSegBlock) {
-        const Partial q = seg_partials[r.first + k];
-        sx = norm_combine<kNorm>(sx, q.sum_xx);
-        su = norm_combine<kNorm>(su, q.sum_uu);
-    }
+__device__ Partial tensor_total(const Partial *__restrict__ partials, SegRange r, bool direct) {
+    constexpr int kSegWaves = kSegBlock / 64;
     __shared__ Partial total;
-    block_combine<kNorm, kSegBlock / 64>(sx, su, &total);
-    __syncthreads();
+    if (direct) {
+        constexpr int kTeams = kDirectBlock / kSegBlock;
+        constexpr int kAtOnce = kNorm == kLinf ? 1 : 2;  // (two spill with its NaN checks)
+        __shared__ Partial red[kDirectSegs][kSegWaves];
+        const int n_segs = (r.count + kSegChunks - 1) / kSegChunks;
+        const int k0 = int(threadIdx.x % kSegBlock);
+        for (int s = threadIdx.x / kSegBlock; s < n_segs; s += kAtOnce * kTeams) {
+            SegmentShare share[kAtOnce];
+#pragma unroll
+            for (int h = 0; h < kAtOnce; ++h) {
+                const int32_t at = (s + h * kTeams) * kSegChunks;
+                const int32_t left = r.count - at;
+                share[h].load(partials + r.first + at, left < kSegChunks ? left : kSegChunks, k0);
+            }
+#pragma unroll
+            for (int h = 0; h < kAtOnce; ++h) {
+                if (s + h * kTeams < n_segs) {
+                    Partial q = share[h].template combine<kNorm>();
+                    q.sum_xx = wave_combine<kNorm>(q.sum_xx);
+                    q.sum_uu = wave_combine<kNorm>(q.sum_uu);
+                    if (threadIdx.x % 64 == 0)
+                        red[s + h * kTeams][threadIdx.x / 64 % kSegWaves] = q;
+                }
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            Partial q{0.0, 0.0};
+            if (int(threadIdx.x) < n_segs) {
+                q = red[threadIdx.x][0];
+#pragma unroll
+                for (int w = 1; w < kSegWaves; ++w) {
+                    q.sum_xx = norm_combine<kNorm>(q.sum_xx, red[threadIdx.x][w].sum_xx);
+                    q.sum_uu = norm_combine<kNorm>(q.sum_uu, red[threadIdx.x][w].sum_uu);
+                }
+            }
+            q.sum_xx = wave_combine<kNorm>(q.sum_xx);
+            q.sum_uu = wave_combine<kNorm>(q.sum_uu);
+            if (threadIdx.x == 0)
+                total = q;
+        }
+    } else {
+        double sx = 0.0, su = 0.0;
+        for (int k = threadIdx.x; k < r.count; k += kSegBlock) {
+            const Partial q = partials[r.first + k];
+            sx = norm_combine<kNorm>(sx, q.sum_xx);
+            su = norm_combine<kNorm>(su, q.sum_uu);
+        }
+        block_combine<kNorm, kSegWaves>(sx, su, &total);
+    }
     return total;
 }
 
 template <int kNorm>
-__global__ __launch_bounds__(kSegBlock) void finalize_kernel(
-    const TensorDesc *__restrict__ tensors, const Partial *__restrict__ seg_partials,
-    const SegRange *__restrict__ ranges, FinalizeArgs a, float *__restrict__ scale,
+__global__ __launch_bounds__(kDirectBlock) void finalize_kernel(
+    const TensorDesc *__restrict__ tensors, const Partial *__restrict__ partials,
+    const SegRange *__restrict__ ranges, int32_t direct, FinalizeArgs a, float *__restrict__ scale,
     double *__restrict__ ratio_out, double *__restrict__ norms_out, uint32_t *__restrict__ flags) {
     const int i = blockIdx.x;
-    const Partial total = tensor_total<kNorm>(seg_partials, ranges[i]);
+    const int32_t out = tensors[i].out_index;
+    const Partial total = tensor_total<kNorm>(partials, ranges[i], direct != 0);
     if (threadIdx.x == 0) {
-        scale[i] = finish_layer<kNorm>(total, a, tensors[i].out_index, ratio_out, norms_out);
+        scale[i] = finish_layer<kNorm>(total, a, out, ratio_out, norms_out);
         // Deferred mode: hand the moment pass's non-finite verdict to the apply
         // pass and clear the word the next moment pass raises.
         if (flags && i == 0) {
@@ -760,12 +826,12 @@ __global__ __launch_bounds__(kSegBlock) void finalize_kernel(
 // ---------------------------------------------------------------------------
 
 template <int kNorm>
-__global__ __launch_bounds__(kSegBlock) void totals_kernel(
-    const Partial *__restrict__ seg_partials, const SegRange *__restrict__ ranges,
+__global__ __launch_bounds__(kDirectBlock) void totals_kernel(
+    const Partial *__restrict__ partials, const SegRange *__restrict__ ranges, int32_t direct,
     int32_t n_tensors, double *__restrict__ totals, uint32_t *__restrict__ flags,
     const uint32_t *__restrict__ ctl, int32_t verdict_mode) {
     const int i = blockIdx.x;
-    const Partial total = tensor_total<kNorm>(seg_partials, ranges[i]);
+    const Partial total = tensor_total<kNorm>(partials, ranges[i], direct != 0);
     if (threadIdx.x == 0) {
         totals[2 * i] = total.sum_xx;
         totals[2 * i + 1] = total.sum_uu;
@@ -1873,6 +1939,38 @@ hipError_t launch_segments(NormKind norm, const Partial *partials, const SegDesc
     return hipLaunchKernel(fn, dim3(n_segs), dim3(kSegBlock), params, 0, stream);
 }
 
+// The per-tensor level over segment partials or, `direct`, chunk partials.
+hipError_t launch_finalize_level(NormKind norm, const TensorDesc *tensors, int32_t n_tensors,
+                                 const Partial *partials, const SegRange *ranges, int32_t direct,
+                                 const FinalizeArgs &args, float *scale, double *ratio_out,
+                                 double *norms_out, uint32_t *flags, hipStream_t stream) {
+    FinalizeArgs a = args;
+    void *params[] = {&tensors, &partials,  &ranges,    &direct, &a,
+                      &scale,   &ratio_out, &norms_out, &flags};
+    const void *fn = norm == kL1     ? reinterpret_cast<const void *>(&finalize_kernel<kL1>)
+                     : norm == kLinf ? reinterpret_cast<const void *>(&finalize_kernel<kLinf>)
+                                     : reinterpret_cast<const void *>(&finalize_kernel<kL2>);
+    return hipLaunchKernel(fn, dim3(n_tensors), dim3(direct ? kDirectBlock : kSegBlock), params,
+                           0, stream);
+}
+
+hipError_t launch_totals_level(NormKind norm, const Partial *partials, const SegRange *ranges,
+                               int32_t direct, int32_t n_tensors, double *totals,
+                               uint32_t *flags, const uint32_t *ctl, int32_t verdict_mode,
+                               hipStream_t stream) {
+    void *params[] = {&partials, &ranges, &direct, &n_tensors,
+                      &totals,   &flags,  &ctl,    &verdict_mode};
+    const void *fn = norm == kL1     ? reinterpret_cast<const void *>(&totals_kernel<kL1>)
+                     : norm == kLinf ? reinterpret_cast<const void *>(&totals_kernel<kLinf>)
+                                     : reinterpret_cast<const void *>(&totals_kernel<kL2>);
+    return hipLaunchKernel(fn, dim3(n_tensors), dim3(direct ? kDirectBlock : kSegBlock), params,
+                           0, stream);
+}
+
+bool totals_verdict_ok(int32_t mode, const uint32_t *ctl) {
+    return mode >= kVerdictZero && mode <= kVerdictCopy && (mode != kVerdictCopy || ctl);
+}
+
 }  // namespace
 
 hipError_t launch_finalize(NormKind norm, const TensorDesc *tensors, int32_t n_tensors,
@@ -1880,33 +1978,41 @@ hipError_t launch_finalize(NormKind norm, const TensorDesc *tensors, int32_t n_t
                            const SegRange *ranges, Partial *seg_partials,
                            const FinalizeArgs &args, float *scale, double *ratio_out,
                            double *norms_out, uint32_t *flags, hipStream_t stream) {
-    hipError_t err = launch_segments(norm, partials, segs, n_segs, seg_partials, stream);
+    const hipError_t err = launch_segments(norm, partials, segs, n_segs, seg_partials, stream);
     if (err != hipSuccess)
         return err;
-    FinalizeArgs a = args;
-    void *params[] = {&tensors, &seg_partials, &ranges,    &a,
-                      &scale,   &ratio_out,    &norms_out, &flags};
-    const void *fn = norm == kL1     ? reinterpret_cast<const void *>(&finalize_kernel<kL1>)
-                     : norm == kLinf ? reinterpret_cast<const void *>(&finalize_kernel<kLinf>)
-                                     : reinterpret_cast<const void *>(&finalize_kernel<kL2>);
-    return hipLaunchKernel(fn, dim3(n_tensors), dim3(kSegBlock), params, 0, stream);
+    return launch_finalize_level(norm, tensors, n_tensors, seg_partials, ranges, 0, args, scale,
+                                 ratio_out, norms_out, flags, stream);
+}
+
+hipError_t launch_direct_finalize(NormKind norm, const TensorDesc *tensors, int32_t n_tensors,
+                                  const Partial *partials, const SegRange *spans,
+                                  const FinalizeArgs &args, float *scale, double *ratio_out,
+                                  double *norms_out, uint32_t *flags, hipStream_t stream) {
+    return launch_finalize_level(norm, tensors, n_tensors, partials, spans, 1, args, scale,
+                                 ratio_out, norms_out, flags, stream);
 }
 
 hipError_t launch_totals(NormKind norm, const Partial *partials, const SegDesc *segs,
                          int32_t n_segs, const SegRange *ranges, int32_t n_tensors,
                          Partial *seg_partials, double *totals, uint32_t *flags,
                          const uint32_t *ctl, int32_t verdict_mode, hipStream_t stream) {
-    if (verdict_mode < kVerdictZero || verdict_mode > kVerdictCopy ||
-        (verdict_mode == kVerdictCopy && !ctl))
+    if (!totals_verdict_ok(verdict_mode, ctl))
         return hipErrorInvalidValue;
-    hipError_t err = launch_segments(norm, partials, segs, n_segs, seg_partials, stream);
+    const hipError_t err = launch_segments(norm, partials, segs, n_segs, seg_partials, stream);
     if (err != hipSuccess)
         return err;
-    void *params[] = {&seg_partials, &ranges, &n_tensors, &totals, &flags, &ctl, &verdict_mode};
-    const void *fn = norm == kL1     ? reinterpret_cast<const void *>(&totals_kernel<kL1>)
-                     : norm == kLinf ? reinterpret_cast<const void *>(&totals_kernel<kLinf>)
-                                     : reinterpret_cast<const void *>(&totals_kernel<kL2>);
-    return hipLaunchKernel(fn, dim3(n_tensors), dim3(kSegBlock), params, 0, stream);
+    return launch_totals_level(norm, seg_partials, ranges, 0, n_tensors, totals, flags, ctl,
+                               verdict_mode, stream);
+}
+
+hipError_t launch_direct_totals(NormKind norm, const Partial *partials, const SegRange *spans,
+                                int32_t n_tensors, double *totals, uint32_t *flags,
+                                const uint32_t *ctl, int32_t verdict_mode, hipStream_t stream) {
+    if (!totals_verdict_ok(verdict_mode, ctl))
+        return hipErrorInvalidValue;
+    return launch_totals_level(norm, partials, spans, 1, n_tensors, totals, flags, ctl,
+                               verdict_mode, stream);
 }
 
 hipError_t launch_scale(NormKind norm, const double *totals, int32_t n_tensors,

@@ -81,26 +81,34 @@ inline StaticTables static_tables(char *base) {
 
 // One tensor of a table batch: the caller's buffers plus where its chunks
 // and segments start in the fine and the coarse table (host-computed
-// prefixes). 64 bytes.
+// prefixes, packed). 48 bytes.
 struct TableEntry {
     float *x;
     const void *g;
     float *m;
     float *v;
-    int64_t numel;
-    int32_t wd;
-    int32_t first_chunk;
-    int32_t first_coarse;
-    int32_t first_seg;
-    int32_t first_cseg;
-    int32_t reserved;
+    uint64_t numel_wd;  // numel in the low 63 bits, wd in the highest
+    uint64_t first;     // pack_first()
 };
-static_assert(sizeof(TableEntry) == 64, "TableEntry layout");
+static_assert(sizeof(TableEntry) == 48, "TableEntry layout");
 
-// Up to kTableBatch tensors, passed to the table kernel by value (3 KB of
-// kernel arguments): the step's tables reach the device with no copy and no
-// buffer of their own.
-constexpr int kTableBatch = 48;
+constexpr int kFirstChunkBits = 20, kFirstCoarseBits = 18, kFirstSegBits = 13;
+static_assert(kStaticMaxChunks < 1 << kFirstChunkBits && kStaticMaxCoarse < 1 << kFirstCoarseBits &&
+                  kStaticMaxSegs < 1 << kFirstSegBits &&
+                  kFirstChunkBits + kFirstCoarseBits + 2 * kFirstSegBits <= 64,
+              "the prefixes fit one word");
+constexpr uint64_t pack_first(int32_t chunk, int32_t coarse, int32_t seg, int32_t cseg) {
+    return uint64_t(chunk) | uint64_t(coarse) << kFirstChunkBits |
+           uint64_t(seg) << (kFirstChunkBits + kFirstCoarseBits) |
+           uint64_t(cseg) << (kFirstChunkBits + kFirstCoarseBits + kFirstSegBits);
+}
+
+// Up to kTableBatch tensors, passed to the table kernel by value (just under
+// 4 KB of kernel arguments): the step's tables reach the device with no copy
+// and no buffer of their own. A launch takes 4 to 5 us, so an entry is packed:
+// 82 fit instead of 48. ResNet-50 (161 tensors) needs 2 launches instead of 4;
+// with the one-kernel finalize its planless step went 183.6 -> 174.5 us.
+constexpr int kTableBatch = 82;
 struct TableBatch {
     TableEntry e[kTableBatch];
     int32_t count;        // entries used
@@ -108,6 +116,9 @@ struct TableBatch {
     int32_t chunk_elems;
     int32_t coarse_elems;
 };
+
+// Workgroups that share one tensor's stretch of the chunk tables.
+constexpr int kTableSplit = 4;
 
 }  // namespace
 }  // namespace lamb_mi355x
@@ -122,52 +133,70 @@ namespace lamb_mi355x {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Tables of a planless step, written from a batch passed by value: workgroup
-// e writes tensor first_index + e's descriptor and segment ranges and fills
-// its stretch of the fine and coarse chunk tables and of both segment lists.
+// Tables of a planless step, written from a batch passed by value: workgroups
+// (e, 0) to (e, kTableSplit - 1) write tensor first_index + e's descriptor and
+// segment ranges and fill its stretch of the fine and coarse chunk tables and
+// of both segment lists. `spans`: the step finalizes in one kernel, which reads
+// chunk spans in the ranges' place and no segment lists.
 // ---------------------------------------------------------------------------
 
-__global__ __launch_bounds__(kBlock) void table_kernel(TableBatch b, StaticTables t) {
+static_assert(sizeof(TableBatch) + sizeof(StaticTables) + 8 <= 4096, "kernel arguments");
+
+__global__ __launch_bounds__(kBlock) void table_kernel(TableBatch b, StaticTables t,
+                                                       int32_t spans) {
     const int e = blockIdx.x;
     const TableEntry &r = b.e[e];
     const int32_t i = b.first_index + e;
-    const int32_t nc = int32_t((r.numel + b.chunk_elems - 1) / b.chunk_elems);
-    const int32_t ncc = int32_t((r.numel + b.coarse_elems - 1) / b.coarse_elems);
+    const int64_t numel = int64_t(r.numel_wd & ~(uint64_t(1) << 63));
+    const int32_t nc = int32_t((numel + b.chunk_elems - 1) / b.chunk_elems);
+    const int32_t ncc = int32_t((numel + b.coarse_elems - 1) / b.coarse_elems);
     const int32_t ns = (nc + kSegChunks - 1) / kSegChunks;
     const int32_t ncs = (ncc + kSegChunks - 1) / kSegChunks;
-    if (threadIdx.x == 0) {
+    uint64_t w = r.first;
+    auto take = [&](int bits) {
+        const int32_t f = int32_t(w & ((uint64_t(1) << bits) - 1));
+        w >>= bits;
+        return f;
+    };
+    const int32_t first_chunk = take(kFirstChunkBits), first_coarse = take(kFirstCoarseBits);
+    const int32_t first_seg = take(kFirstSegBits), first_cseg = take(kFirstSegBits);
+    if (blockIdx.y == 0 && threadIdx.x == 0) {
         TensorDesc d;
         d.x = r.x;
         d.g = r.g;
         d.m = r.m;
         d.v = r.v;
         d.x_copy = nullptr;
-        d.numel = r.numel;
-        d.wd = r.wd;
-        d.first_chunk = r.first_chunk;
-        d.first_coarse = r.first_coarse;
+        d.numel = numel;
+        d.wd = int32_t(r.numel_wd >> 63);
+        d.first_chunk = first_chunk;
+        d.first_coarse = first_coarse;
         d.out_index = i;
         t.tensors[i] = d;
-        t.ranges[0][i] = SegRange{r.first_seg, ns};
-        t.ranges[1][i] = SegRange{r.first_cseg, ncs};
+        t.ranges[0][i] = spans ? SegRange{first_chunk, nc} : SegRange{first_seg, ns};
+        t.ranges[1][i] = spans ? SegRange{first_coarse, ncc} : SegRange{first_cseg, ncs};
     }
-    if (i == 0 && threadIdx.x < 64) {
+    if (i == 0 && blockIdx.y == 0 && threadIdx.x < 64) {
         t.flags[threadIdx.x] = 0u;
         t.ctl[threadIdx.x] = 0u;
     }
-    for (int32_t k = threadIdx.x; k < nc; k += kBlock)
-        t.ids[r.first_chunk + k] = i;
-    for (int32_t k = threadIdx.x; k < ncc; k += kBlock)
-        t.coarse_ids[r.first_coarse + k] = i;
-    for (int32_t k = threadIdx.x; k < ns; k += kBlock) {
+    const int32_t k0 = int32_t(blockIdx.y) * kBlock + int32_t(threadIdx.x);
+    constexpr int32_t kStep = kTableSplit * kBlock;
+    for (int32_t k = k0; k < nc; k += kStep)
+        t.ids[first_chunk + k] = i;
+    for (int32_t k = k0; k < ncc; k += kStep)
+        t.coarse_ids[first_coarse + k] = i;
+    if (spans)
+        return;  // no segment lists
+    for (int32_t k = k0; k < ns; k += kStep) {
         const int32_t left = nc - k * kSegChunks;
-        t.segs[0][r.first_seg + k] =
-            SegDesc{r.first_chunk + k * kSegChunks, left < kSegChunks ? left : kSegChunks};
+        t.segs[0][first_seg + k] =
+            SegDesc{first_chunk + k * kSegChunks, left < kSegChunks ? left : kSegChunks};
     }
-    for (int32_t k = threadIdx.x; k < ncs; k += kBlock) {
+    for (int32_t k = k0; k < ncs; k += kStep) {
         const int32_t left = ncc - k * kSegChunks;
-        t.segs[1][r.first_cseg + k] =
-            SegDesc{r.first_coarse + k * kSegChunks, left < kSegChunks ? left : kSegChunks};
+        t.segs[1][first_cseg + k] =
+            SegDesc{first_coarse + k * kSegChunks, left < kSegChunks ? left : kSegChunks};
     }
 }
 
@@ -202,13 +231,15 @@ hipError_t static_scratch(char **base) {
 // Writes the batch's tensors into the tables at `t`: descriptors, chunk ids,
 // segments and segment ranges of both tables; the batch holding tensor 0
 // also clears the flag and control words.
-hipError_t launch_table(const TableBatch &batch, const StaticTables &t, hipStream_t stream) {
+hipError_t launch_table(const TableBatch &batch, const StaticTables &t, bool direct,
+                        hipStream_t stream) {
     if (batch.count < 1 || batch.count > kTableBatch)
         return hipErrorInvalidValue;
     TableBatch b = batch;
     StaticTables tables = t;
-    void *params[] = {&b, &tables};
-    return hipLaunchKernel(reinterpret_cast<const void *>(&table_kernel), dim3(b.count),
+    int32_t spans = direct ? 1 : 0;
+    void *params[] = {&b, &tables, &spans};
+    return hipLaunchKernel(reinterpret_cast<const void *>(&table_kernel), dim3(b.count, kTableSplit),
                            dim3(kBlock), params, 0, stream);
 }
 
@@ -250,10 +281,11 @@ lamb_status lamb_step_static(const lamb_tensor *tensors, int32_t n_tensors, int3
     }
     const int32_t coarse =
         int32_t(std::min<int64_t>(int64_t(chunk) * kCoarseFactor, kMaxChunkElems));
-    int64_t n_chunks = 0, n_coarse = 0;
+    int64_t n_chunks = 0, n_coarse = 0, largest = 0;
     for (int32_t i = 0; i < n_tensors; ++i) {
         n_chunks += (tensors[i].numel + chunk - 1) / chunk;
         n_coarse += (tensors[i].numel + coarse - 1) / coarse;
+        largest = std::max(largest, tensors[i].numel);
         if (n_chunks > kStaticMaxChunks)
             return fail(LAMB_EINVAL, "more than %d chunks of %d elements (at most %d chunks "
                         "without a plan); raise chunk_elems", kStaticMaxChunks, chunk,
@@ -269,6 +301,9 @@ lamb_status lamb_step_static(const lamb_tensor *tensors, int32_t n_tensors, int3
     if (err != hipSuccess)
         return fail_hip(err, "looking up the static device array");
     const StaticTables t = static_tables(base);
+    const int seg = kind.deferred ? 1 : 0;
+    const bool direct =
+        largest <= int64_t(kDirectSegs) * kSegChunks * (kind.deferred ? coarse : chunk);
     hipStream_t s = static_cast<hipStream_t>(stream);
     // The tables, batch by batch, as kernel arguments.
     TableBatch b;
@@ -287,19 +322,14 @@ lamb_status lamb_step_static(const lamb_tensor *tensors, int32_t n_tensors, int3
         e.g = src.g;
         e.m = src.m;
         e.v = needs_v ? src.v : nullptr;
-        e.numel = src.numel;
-        e.wd = src.wd;
-        e.first_chunk = first_chunk;
-        e.first_coarse = first_coarse;
-        e.first_seg = first_seg;
-        e.first_cseg = first_cseg;
-        e.reserved = 0;
+        e.numel_wd = uint64_t(src.numel) | uint64_t(src.wd != 0) << 63;
+        e.first = pack_first(first_chunk, first_coarse, first_seg, first_cseg);
         first_chunk += nc;
         first_coarse += ncc;
         first_seg += (nc + kSegChunks - 1) / kSegChunks;
         first_cseg += (ncc + kSegChunks - 1) / kSegChunks;
         if (b.count == kTableBatch || i == n_tensors - 1) {
-            err = launch_table(b, t, s);
+            err = launch_table(b, t, direct, s);
             if (err != hipSuccess)
                 return fail_hip(err, "launching the table kernel");
             b.count = 0;
@@ -312,10 +342,14 @@ lamb_status lamb_step_static(const lamb_tensor *tensors, int32_t n_tensors, int3
                          two_pass_threads(moment_elems), t.flags, t.ctl, kGuardNone, a, s);
     if (err != hipSuccess)
         return fail_hip(err, "launching the moment kernel");
-    const int seg = kind.deferred ? 1 : 0;
-    err = launch_finalize(kind.norm, t.tensors, n_tensors, t.partials, t.segs[seg],
-                          kind.deferred ? first_cseg : first_seg, t.ranges[seg], t.seg_partials,
-                          f, t.scale, ratio_out, norms_out, kind.deferred ? t.flags : nullptr, s);
+    uint32_t *flags = kind.deferred ? t.flags : nullptr;
+    if (direct)
+        err = launch_direct_finalize(kind.norm, t.tensors, n_tensors, t.partials, t.ranges[seg],
+                                     f, t.scale, ratio_out, norms_out, flags, s);
+    else
+        err = launch_finalize(kind.norm, t.tensors, n_tensors, t.partials, t.segs[seg],
+                              kind.deferred ? first_cseg : first_seg, t.ranges[seg],
+                              t.seg_partials, f, t.scale, ratio_out, norms_out, flags, s);
     if (err != hipSuccess)
         return fail_hip(err, "launching the finalize kernel");
     err = launch_apply(kind, t.tensors, t.ids, chunk, t.scale, int32_t(n_chunks),
