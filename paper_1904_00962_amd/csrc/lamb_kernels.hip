@@ -691,10 +691,10 @@ __global__ __launch_bounds__(kBlock) void finite_kernel(const TensorDesc *__rest
 // in flight) when no tensor of the table has more than kDirectSegs segments,
 // and in two kernels otherwise, same bits either way. The levels take no
 // bandwidth to speak of: they cost their launches and dependent loads.
-// Of BERT-Large's 1/8 share (up to 8 segments a tensor) one kernel takes 6.2 us,
-// two took 9.5, and the split step went 257.3 -> 253.9 us; ResNet-50's planless
-// step 5.2 against 9 us. Tensors of many segments (a 23M-element embedding: 45)
-// are faster spread over workgroups.
+// One kernel takes 5.9 us on BERT-Large's 1/8 share (up to 8 segments a tensor)
+// and 5.1 on ResNet-50; of two, each takes 4.7 to 5.3 (traced on BERT-Base). The
+// split step went 257.3 -> 253.9 us. Past 16 segments the loop's trips, each a
+// round of loads, would add up (a 23M-element embedding has 45 segments).
 // ---------------------------------------------------------------------------
 
 // A thread's share of one segment's partials: slots k0 + j * kSegBlock of the
