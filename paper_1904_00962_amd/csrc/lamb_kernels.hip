@@ -1130,10 +1130,19 @@ __device__ __forceinline__ f32x4 use_group(const LayerStreams<kAlgo, kBf16> &lay
 
 // The layer's last 1 to 3 elements, when it does not end at a float4: one
 // thread of the one tile that holds its last block reads and updates them
-// here, keeps x and u in LDS, and writes x with write_tail.
+// here, keeps x and u in LDS, and writes x with write_tail. No barrier lies
+// between a tile's writes and the reads of the workgroup's next tile, whose
+// tail is another thread's: that thread may be ahead by then. So a workgroup
+// has two TailElems and its tiles take them in turn (next_tail); between two
+// uses of one lie all barriers of the tile in between.
 struct TailElems {
     float x[4], u[4];
 };
+
+__device__ __forceinline__ TailElems &next_tail(TailElems (&pair)[2], uint32_t &turn) {
+    turn ^= 1u;
+    return pair[turn];
+}
 
 __device__ __forceinline__ int tail_len(const TileDesc &d) {
     const bool mine = (d.shape & kTileRagged) != 0 &&
@@ -1258,7 +1267,7 @@ void fused_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
     constexpr int kInLds = kGroups < kLdsGroups ? kGroups : kLdsGroups;
     constexpr int kInRegs = kGroups - kInLds;
     __shared__ f32x4 sh_x[kInLds][kBlock];
-    __shared__ TailElems sh_tail;
+    __shared__ TailElems sh_tail[2];
     if (threadIdx.x == 0) {
         sh_epoch = ctl_load(ctl + kCtlEpoch);
         sh_fault = ctl_load(ctl + kCtlFault);
@@ -1281,6 +1290,7 @@ void fused_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
     // streaming through the wait. p_j: the entry it belongs to (-1: none).
     f32x4 px = {0.0f, 0.0f, 0.0f, 0.0f}, pg = px, pm = px, pv = px;
     int32_t p_j = -1;
+    uint32_t tail_turn = 0;
     for (int32_t r = 0; !stop; ++r) {
         const int32_t j = r * grid + static_cast<int32_t>(blockIdx.x);  // entry of round r
         if (j >= n_tiles)
@@ -1296,6 +1306,7 @@ void fused_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
         gfloat *v = kV ? global_view(t.v) : nullptr;
         const GradView<kBf16> g(t.g, 0, a.grad_scale);
         const float lam = (t.shape & kTileWd) ? a.weight_decay : 0.0f;
+        TailElems &kept = next_tail(sh_tail, tail_turn);
         // Group k of this thread: 4 elements from `first`, `valid` (0-4) of them
         // inside the layer.
         auto group = [&](int k, uint32_t &first, int &valid) {
@@ -1416,7 +1427,7 @@ void fused_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
                     x_keep[k - kInLds] = us[k];
             });
             if (const int tail = tail_len(t))
-                read_tail<kAlgo, kNorm, kBf16>(t, tail, lam, a, sh_tail, sum_xx, sum_uu);
+                read_tail<kAlgo, kNorm, kBf16>(t, tail, lam, a, kept, sum_xx, sum_uu);
         }
         block_combine<kNorm, kWaves>(sum_xx, sum_uu, &sh_tile);
         __syncthreads();
@@ -1505,7 +1516,7 @@ void fused_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     xn[e] = valid == 4  ? fmaf(-s, us[k][e], xo[e])
-                            : e < valid ? fmaf(-s, sh_tail.u[e], sh_tail.x[e])
+                            : e < valid ? fmaf(-s, kept.u[e], kept.x[e])
                                         : 0.0f;
                 if (valid == 4) {
                     store4_at(x, at, xn);
@@ -1580,7 +1591,7 @@ void quick_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
     constexpr int kUnrollF = kFusedUnroll<kAlgo>;
     __shared__ uint32_t sh_epoch, sh_fault, sh_skip, sh_stop;
     __shared__ float sh_scale;
-    __shared__ TailElems sh_tail;
+    __shared__ TailElems sh_tail[2];
     __shared__ Partial sh_tile[kWaves], sh_layer[kWaves];
     // The tile's x waits in LDS (32 KB for the first kLdsGroups groups) and,
     // past those, in registers; its update direction waits in registers.
@@ -1616,6 +1627,7 @@ void quick_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
     uint64_t *cur_u = cur_x + n, *cur_scale = cur_u + n;
     uint64_t *next_u = next_x + n, *next_scale = next_u + n;
 
+    uint32_t tail_turn = 0;
     for (bool stop = sh_fault != 0 || sh_skip != 0; !stop && j < n_tiles;) {
         const int32_t jn = j + grid;
         TileDesc dn = {};  // the next round's tile (nothing past the last round)
@@ -1634,6 +1646,7 @@ void quick_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
         const float lam = d.shape & kTileWd ? a.weight_decay : 0.0f;
         const int groups = int(d.shape >> kTileGroupsShift);
         const uint32_t end = uint32_t(d.numel & ~3) * 4u;  // byte past the whole float4s
+        TailElems &kept = next_tail(sh_tail, tail_turn);
 
         // Read once, write the new moments, keep x and u. A ring of two trips'
         // groups: the next trip's loads are issued before this trip's groups
@@ -1674,7 +1687,7 @@ void quick_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
         });
         const int tail = tail_len(d);
         if (tail)
-            read_tail<kAlgo, kNorm, kBf16>(d, tail, lam, a, sh_tail, sum_xx, sum_uu);
+            read_tail<kAlgo, kNorm, kBf16>(d, tail, lam, a, kept, sum_xx, sum_uu);
         block_reduce<kNorm>(sum_xx, sum_uu, sh_tile);
         if (trace)
             stamp[1] = __builtin_amdgcn_s_memrealtime();
@@ -1755,7 +1768,7 @@ void quick_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
             }
         }
         if (tail)
-            write_tail(d, tail, s, sh_tail);
+            write_tail(d, tail, s, kept);
         if (trace && threadIdx.x == 0) {
             trace[4 * j] = stamp[0];
             trace[4 * j + 1] = stamp[1];

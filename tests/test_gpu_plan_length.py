@@ -57,3 +57,39 @@ def test_short_and_long_plans_agree(path, variant, g_dtype, norm, eps):
         pair.close()
     for a, b in zip(*states):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("path", ["auto", "wide"])
+@pytest.mark.parametrize("n,quick", [(3000, True), (11000, False)])
+def test_ragged_layers_in_successive_rounds(path, n, quick):
+    """Layers of 1 to 1023 elements that end in every wave of the workgroup,
+    round after round, on both kernels: against the oracle, and bit for bit
+    against the same layers in plans of one round (x, m, v, bf16 copies)."""
+    torch = H.torch_cuda()
+    rng = np.random.default_rng(n)
+    sizes = [int(4 * k + e) for k, e in zip(rng.integers(0, 256, n), rng.integers(1, 4, n))]
+    xs = [(rng.standard_normal(s) * 0.05).astype(np.float32) for s in sizes]
+    gs = [(rng.standard_normal(s) * 1e-3 + 2e-3).astype(np.float32) for s in sizes]
+    hp = _lib.lamb_hparams_init("lamb", step=1, lr=1e-2)
+    step = 1000  # layers of a plan of one round
+
+    def run(lo, hi, subset):
+        pair = H.Pair(xs[lo:hi], [True] * (hi - lo), "f32", "lamb", oracle_subset=subset,
+                      path=path)
+        copies = [torch.zeros(s + 8, dtype=torch.bfloat16, device="cuda") for s in sizes[lo:hi]]
+        _lib.lamb_plan_set_bf16_copies(pair.plan, [c.data_ptr() for c in copies])
+        rounds = _rounds(pair.plan, sizes[lo:hi])
+        hg = pair.set_grads([torch.from_numpy(g) for g in gs[lo:hi]])
+        tol = pair.ratio_tolerances(hp, hg)
+        ref = H.step_ex_both(pair, hp, hg)
+        pair.compare(ref, "%d ragged layers from %d" % (hi - lo, lo), tol)
+        state = [torch.cat([t.float() for t in part]) for part in (pair.X, pair.M, pair.V, copies)]
+        pair.close()
+        return state, rounds
+
+    whole, rounds = run(0, n, range(0, n, 43))
+    assert rounds >= 2 and (rounds <= QUICK_ROUNDS) == quick
+    parts = [run(lo, lo + step, []) for lo in range(0, n, step)]
+    assert all(r <= 1 for _, r in parts)
+    for k, a in enumerate(whole):
+        assert torch.equal(a, torch.cat([p[0][k] for p in parts]))
