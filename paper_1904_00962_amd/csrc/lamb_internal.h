@@ -242,12 +242,10 @@ hipError_t launch_finalize(NormKind norm, const TensorDesc *tensors, int32_t n_t
                            double *norms_out, uint32_t *flags, hipStream_t stream);
 // The same in one kernel, for a table whose tensors have at most kDirectSegs
 // segments each (the caller checks); `spans`: every tensor's chunk partials.
-// Weak, as launch_single_pass below.
 hipError_t launch_direct_finalize(NormKind norm, const TensorDesc *tensors, int32_t n_tensors,
                                   const Partial *partials, const SegRange *spans,
                                   const FinalizeArgs &args, float *scale, double *ratio_out,
-                                  double *norms_out, uint32_t *flags, hipStream_t stream)
-    __attribute__((weak));
+                                  double *norms_out, uint32_t *flags, hipStream_t stream);
 // `check` non-null (direct mode only): also re-sum the partial norms of every
 // chunk from the x read and the u recomputed, into check[chunk].
 hipError_t launch_apply(const StepKind &kind, const TensorDesc *tensors,
@@ -272,8 +270,7 @@ hipError_t launch_totals(NormKind norm, const Partial *partials, const SegDesc *
 // The same in one kernel, as launch_direct_finalize.
 hipError_t launch_direct_totals(NormKind norm, const Partial *partials, const SegRange *spans,
                                 int32_t n_tensors, double *totals, uint32_t *flags,
-                                const uint32_t *ctl, int32_t verdict_mode, hipStream_t stream)
-    __attribute__((weak));
+                                const uint32_t *ctl, int32_t verdict_mode, hipStream_t stream);
 // Split step, second half: per tensor the norms, phi, ratio and scale from
 // combined totals; flags[1] receives the combined verdict for a deferred
 // apply pass.
@@ -304,15 +301,12 @@ constexpr uint64_t kEmptySlot = ~uint64_t(0);
 // round) combines the totals of its head, ext_totals[2 ext] and
 // ext_totals[2 ext + 1], before its own tiles' partials, and writes its step
 // scale to ext_scale[ext] for the apply pass over the head.
-// Weak: a host-only build of lamb_api.cpp (a sanitizer run of its validation)
-// leaves the kernels out.
 hipError_t launch_single_pass(const StepKind &kind, int groups, const TileDesc *tiles,
                               int32_t n_tiles, int32_t grid, uint64_t *slots, uint32_t *ctl,
                               uint32_t *flags, bool guarded, int32_t *nonfinite_out,
                               const StepArgs &args, const FinalizeArgs &fargs,
                               double *ratio_out, double *norms_out, const double *ext_totals,
-                              float *ext_scale, uint64_t *trace, hipStream_t stream)
-    __attribute__((weak));
+                              float *ext_scale, uint64_t *trace, hipStream_t stream);
 // Workgroups of the single-pass kernels for `kind` and tile shape `groups`
 // that fit on one CU at once (the fewer of the two kernels').
 hipError_t fused_blocks_per_cu(const StepKind &kind, int groups, int *blocks);

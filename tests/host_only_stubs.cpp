@@ -1,8 +1,8 @@
 // Kernel launchers for a host-only build of the library's C ABI (the
 // sanitizer test in test_c_abi.py): the host-only entry points it exercises
-// never launch a kernel, so every launcher here just reports failure. The
-// declarations come from the library's internal header, so a signature that
-// drifts fails to compile.
+// never launch a kernel, so every launcher here just reports failure. The test
+// checks that these are all the launchers the host code needs and no others, so
+// one that is missing or whose signature drifts fails there.
 #include "lamb_internal.h"
 
 namespace lamb_mi355x {
@@ -41,10 +41,21 @@ hipError_t launch_finite(bool, const TensorDesc *, const ChunkDesc *, int32_t, u
     return hipErrorNotSupported;
 }
 
-hipError_t launch_fused(const StepKind &, int, const TensorDesc *, const ChunkDesc *, int32_t,
-                        int32_t, uint64_t *, uint32_t *, uint32_t *, bool, int32_t *,
-                        const StepArgs &, const FinalizeArgs &, double *, double *,
-                        const double *, float *, uint64_t *, hipStream_t) {
+hipError_t launch_direct_finalize(NormKind, const TensorDesc *, int32_t, const Partial *,
+                                  const SegRange *, const FinalizeArgs &, float *, double *,
+                                  double *, uint32_t *, hipStream_t) {
+    return hipErrorNotSupported;
+}
+
+hipError_t launch_direct_totals(NormKind, const Partial *, const SegRange *, int32_t, double *,
+                                uint32_t *, const uint32_t *, int32_t, hipStream_t) {
+    return hipErrorNotSupported;
+}
+
+hipError_t launch_single_pass(const StepKind &, int, const TileDesc *, int32_t, int32_t,
+                              uint64_t *, uint32_t *, uint32_t *, bool, int32_t *,
+                              const StepArgs &, const FinalizeArgs &, double *, double *,
+                              const double *, float *, uint64_t *, hipStream_t) {
     return hipErrorNotSupported;
 }
 

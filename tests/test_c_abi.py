@@ -50,6 +50,39 @@ def test_c_program_uses_the_host_entry_points(tmp_path):
     assert "all checks passed" in r.stdout
 
 
+def _symbols(obj):
+    """(type, demangled name) of the object's functions of the library's namespace."""
+    r = subprocess.run(["nm", "-C", str(obj)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    found = [line.split(maxsplit=2 if line[0] != " " else 1) for line in r.stdout.splitlines()]
+    return [(f[-2], f[-1]) for f in found if f[-1].startswith("lamb_mi355x::")]
+
+
+def test_launchers_are_all_required(tmp_path):
+    """Every launcher that the host code calls is an undefined symbol of it that
+    has to resolve (a weak one would link without its kernels and be called
+    through a null address), and tests/host_only_stubs.cpp defines exactly
+    these."""
+    gxx = _compiler("g++")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    if not os.path.exists(os.path.join(rocm, "include", "hip", "hip_runtime_api.h")):
+        pytest.skip("HIP headers not found under %s" % rocm)
+    objects = []
+    for src in (os.path.join(build.CSRC, "lamb_api.cpp"),
+                os.path.join(HERE, "host_only_stubs.cpp")):
+        objects.append(tmp_path / (os.path.basename(src) + ".o"))
+        r = subprocess.run([gxx, "-std=c++17", "-O1", "-fPIC", "-c", "-D__HIP_PLATFORM_AMD__",
+                            "-I", build.INCLUDE, "-I", build.CSRC,
+                            "-I", os.path.join(rocm, "include"), src, "-o", str(objects[-1])],
+                           capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+    api, stubs = (_symbols(o) for o in objects)
+    assert not [s for s in api if s[0] == "w"]
+    needed = {name for kind, name in api if kind == "U"}
+    assert len(needed) > 5
+    assert needed == {name for kind, name in stubs if kind == "T"}
+
+
 def test_host_code_under_sanitizers(tmp_path):
     """The library's host code (lamb_api.cpp: validation, chunk table, tile
     schedule, learning-rate helpers, status strings) built with g++ under
