@@ -66,9 +66,7 @@ struct lamb_plan {
     int fused_per_cu[4][2][3] = {};  // single-pass workgroups per CU by algo, bf16, norm
     std::vector<TensorDesc> host_tensors;  // host image of the tensor table
     std::vector<TensorDesc> host_rest;     // host image of the heads' table
-    std::vector<TileDesc> host_tiles;      // host image of the tile list
     std::vector<int32_t> tile_count;       // tiles of each layer on the single pass
-    std::vector<int32_t> first_tile;       // its first entry in the list
     std::vector<int64_t> single_elems;     // elements of each layer on the single pass
     std::vector<std::pair<uintptr_t, uintptr_t>> ranges;  // sorted buffer ranges of the table
     // finiteness check of skip_nonfinite steps that take the single pass
@@ -952,9 +950,7 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
     plan->n_rest = n_rest;
     plan->n_rest_chunks = n_rest_chunks;
     plan->host_tensors = std::move(host_tensors);
-    plan->host_tiles = std::move(host_tiles);
     plan->tile_count = std::move(tile_count);
-    plan->first_tile = std::move(first_tile);
     plan->host_rest = std::move(host_rest);
     plan->single_elems = std::move(tail);
     for (const BufferRange &r : ranges)
@@ -1345,32 +1341,22 @@ lamb_status lamb_plan_set_bf16_copies(lamb_plan *plan, void *const *copies) {
     std::vector<TensorDesc> next_rest = plan->host_rest;
     for (TensorDesc &r : next_rest)
         r.x_copy = next[size_t(r.out_index)].x_copy;
-    // the single pass's tiles hold the tails of split layers at an offset
-    std::vector<TileDesc> next_tiles = plan->host_tiles;
-    for (int32_t i = 0; i < plan->n_tensors; ++i) {
-        uint16_t *c = next[size_t(i)].x_copy;
-        if (c)
-            c += next[size_t(i)].numel - plan->single_elems[size_t(i)];
-        for (int32_t k = 0; k < plan->tile_count[size_t(i)]; ++k)
-            next_tiles[size_t(plan->first_tile[size_t(i)]) + size_t(k)].x_copy = c;
-    }
     DeviceGuard guard(plan->device);
     if (guard.status != hipSuccess)
         return fail_hip(guard.status, "selecting the plan's device");
     hipError_t err = hipMemcpy(plan->tensors, next.data(),
                                sizeof(TensorDesc) * size_t(plan->n_tensors), hipMemcpyHostToDevice);
-    if (err == hipSuccess && plan->n_tiles > 0)
-        err = hipMemcpy(plan->tiles, next_tiles.data(), sizeof(TileDesc) * next_tiles.size(),
-                        hipMemcpyHostToDevice);
     if (err == hipSuccess && plan->n_rest > 0)
         err = hipMemcpy(plan->rest_tensors, next_rest.data(),
                         sizeof(TensorDesc) * size_t(plan->n_rest), hipMemcpyHostToDevice);
+    // the single pass's tiles take theirs from the tensor table
+    if (err == hipSuccess && plan->n_tiles > 0)
+        err = launch_tile_copies(plan->tiles, plan->n_tiles, plan->tensors, nullptr);
     if (err == hipSuccess)
         err = hipDeviceSynchronize();
     if (err != hipSuccess)
-        return fail_hip(err, "hipMemcpy of the tensor table");
+        return fail_hip(err, "updating the plan's tables");
     plan->host_tensors = std::move(next);
-    plan->host_tiles = std::move(next_tiles);
     plan->host_rest = std::move(next_rest);
     return LAMB_OK;
 }

@@ -307,6 +307,10 @@ hipError_t launch_single_pass(const StepKind &kind, int groups, const TileDesc *
                               const StepArgs &args, const FinalizeArgs &fargs,
                               double *ratio_out, double *norms_out, const double *ext_totals,
                               float *ext_scale, uint64_t *trace, hipStream_t stream);
+// Every tile's x_copy from its layer's in `tensors` (at the tail's offset, for
+// the tail of a split layer).
+hipError_t launch_tile_copies(TileDesc *tiles, int32_t n_tiles, const TensorDesc *tensors,
+                              hipStream_t stream);
 // Workgroups of the single-pass kernels for `kind` and tile shape `groups`
 // that fit on one CU at once (the fewer of the two kernels').
 hipError_t fused_blocks_per_cu(const StepKind &kind, int groups, int *blocks);

@@ -59,6 +59,10 @@ hipError_t launch_single_pass(const StepKind &, int, const TileDesc *, int32_t, 
     return hipErrorNotSupported;
 }
 
+hipError_t launch_tile_copies(TileDesc *, int32_t, const TensorDesc *, hipStream_t) {
+    return hipErrorNotSupported;
+}
+
 hipError_t fused_blocks_per_cu(const StepKind &, int, int *) { return hipErrorNotSupported; }
 
 }  // namespace lamb_mi355x

@@ -337,3 +337,33 @@ def test_bf16_copy_guard_bands_and_detach(path):
         assert e.value.status == _lib.LAMB_EOVERLAP
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("path", ["auto", "wide"])
+def test_bf16_copies_attached_and_detached_in_turn(path):
+    """A split layer (its tail's tiles write the copy at an offset), layers of
+    several tiles and of one, over several rounds: after every change of the
+    attached copies a step writes these and no others."""
+    torch = H.torch_cuda()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    sizes = [4 * cus * 10240 + 1029, 3 * cus * 8192 + 2, 2 * cus * 8192, 70001, 513, 7]
+    rng = np.random.default_rng(23)
+    xs = [torch.from_numpy((rng.standard_normal(n) * 0.5).astype(np.float32)) for n in sizes]
+    pair = H.Pair(xs, [True] * len(sizes), "bf16", "lamb", oracle_subset=[], path=path)
+    copies = [torch.full((n,), -1.0, dtype=torch.bfloat16, device="cuda") for n in sizes]
+    try:
+        assert _lib.lamb_plan_tiles(pair.plan, True)[3][0] < sizes[0]
+        for t, on in enumerate([(0, 1, 3, 5), (), (2, 3, 4), (0, 1, 2, 3, 4, 5)], start=1):
+            for c in copies:
+                c.fill_(-1.0)
+            _lib.lamb_plan_set_bf16_copies(
+                pair.plan, [c.data_ptr() if i in on else 0 for i, c in enumerate(copies)])
+            pair.set_grads(_grads(rng, pair.X, "bf16"))
+            _lib.lamb_step_ex(pair.plan, _hp("lamb", step=t),
+                              torch.cuda.current_stream().cuda_stream, 0, 0, 0)
+            for i, c in enumerate(copies):
+                want = pair.X[i].to(torch.bfloat16) if i in on else torch.full_like(c, -1.0)
+                assert torch.equal(c.view(torch.int16), want.view(torch.int16)), (t, i)
+        _lib.lamb_plan_check(pair.plan)
+    finally:
+        pair.close()
