@@ -61,7 +61,7 @@ struct lamb_plan {
     SegDesc *segs[3] = {};
     SegRange *seg_ranges[3] = {};
     int32_t n_segs[3] = {};
-    bool direct_segs[3] = {};  // no tensor has more than kDirectSegs segments
+    int32_t seg_teams[3] = {};  // direct_teams() of each table
     Partial *seg_partials = nullptr;
     int fused_per_cu[4][2][3] = {};  // single-pass workgroups per CU by algo, bf16, norm
     std::vector<TensorDesc> host_tensors;  // host image of the tensor table
@@ -554,34 +554,37 @@ std::vector<int32_t> chunk_ids_of(const std::vector<int64_t> &numel, int32_t chu
 }
 
 // Finalize segments of a chunk table: tensor k's chunk partials
-// [first_k, first_k + count_k) cut into runs of kSegChunks. Returns whether the
-// table finalizes in one kernel: `segs` is empty then, and `ranges` are the
-// tensors' chunk spans.
-bool build_segments(const std::vector<std::pair<int32_t, int32_t>> &tensor_chunks,
-                    std::vector<SegDesc> *segs, std::vector<SegRange> *ranges) {
+// [first_k, first_k + count_k) cut into runs of kSegChunks. Returns the teams of
+// a table that finalizes in one kernel: `segs` is empty then, and `ranges` are
+// the tensors' chunk spans.
+int32_t build_segments(const std::vector<std::pair<int32_t, int32_t>> &tensor_chunks,
+                       std::vector<SegDesc> *segs, std::vector<SegRange> *ranges) {
     segs->clear();
     ranges->clear();
-    if (std::all_of(tensor_chunks.begin(), tensor_chunks.end(),
-                    [](const auto &tc) { return tc.second <= kDirectSegs * kSegChunks; })) {
-        for (const auto &tc : tensor_chunks)
-            ranges->push_back(SegRange{tc.first, tc.second});
-        return true;
-    }
+    int64_t widest = 0;
+    for (const auto &tc : tensor_chunks)
+        widest = std::max(widest, (int64_t(tc.second) + kSegChunks - 1) / kSegChunks);
+    const int32_t teams = direct_teams(int64_t(tensor_chunks.size()), widest);
     for (const auto &tc : tensor_chunks) {
+        if (teams > 0) {
+            ranges->push_back(SegRange{tc.first, tc.second});
+            continue;
+        }
         const int32_t first_seg = int32_t(segs->size());
         for (int32_t k = 0; k < tc.second; k += kSegChunks)
             segs->push_back(SegDesc{tc.first + k, std::min(kSegChunks, tc.second - k)});
         ranges->push_back(SegRange{first_seg, int32_t(segs->size()) - first_seg});
     }
-    return false;
+    return teams;
 }
 
 // The totals of the `n` tensors of segment table `seg`.
 hipError_t plan_totals(const lamb_plan *plan, int seg, NormKind norm, int32_t n, double *totals,
                        VerdictMode verdict, hipStream_t s) {
-    if (plan->direct_segs[seg])
-        return launch_direct_totals(norm, plan->partials, plan->seg_ranges[seg], n, totals,
-                                    plan->flags, plan->ctl, verdict, s);
+    if (plan->seg_teams[seg] > 0)
+        return launch_direct_totals(norm, plan->seg_teams[seg], plan->partials,
+                                    plan->seg_ranges[seg], n, totals, plan->flags, plan->ctl,
+                                    verdict, s);
     return launch_totals(norm, plan->partials, plan->segs[seg], plan->n_segs[seg],
                          plan->seg_ranges[seg], n, plan->seg_partials, totals, plan->flags,
                          plan->ctl, verdict, s);
@@ -776,7 +779,7 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
     const int32_t n_rest_chunks = int32_t(host_rest_ids.size());
     std::vector<SegDesc> host_segs[3];
     std::vector<SegRange> host_ranges[3];
-    bool direct_segs[3];
+    int32_t seg_teams[3];
     {
         std::vector<std::pair<int32_t, int32_t>> fine, coarse_tc, rest;
         auto chunks = [](const TensorDesc &d, int32_t elems) {
@@ -788,11 +791,11 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
         }
         for (const TensorDesc &d : host_rest)
             rest.emplace_back(d.first_chunk, chunks(d, chunk));
-        direct_segs[kSegFine] =
+        seg_teams[kSegFine] =
             build_segments(fine, &host_segs[kSegFine], &host_ranges[kSegFine]);
-        direct_segs[kSegCoarse] =
+        seg_teams[kSegCoarse] =
             build_segments(coarse_tc, &host_segs[kSegCoarse], &host_ranges[kSegCoarse]);
-        direct_segs[kSegRest] =
+        seg_teams[kSegRest] =
             build_segments(rest, &host_segs[kSegRest], &host_ranges[kSegRest]);
     }
     size_t max_segs = 1;
@@ -871,7 +874,7 @@ lamb_status lamb_plan_create(const lamb_tensor *tensors, int32_t n_tensors,
         plan->seg_ranges[k] = reinterpret_cast<SegRange *>(base);
         base += range_bytes[k];
         plan->n_segs[k] = int32_t(host_segs[k].size());
-        plan->direct_segs[k] = direct_segs[k];
+        plan->seg_teams[k] = seg_teams[k];
     }
     plan->seg_partials = reinterpret_cast<Partial *>(base);
     base += seg_partial_bytes;
@@ -1239,10 +1242,10 @@ lamb_status lamb_step_ex(lamb_plan *plan, const lamb_hparams *hp, void *stream,
         mark(plan, kTimedMoments, s);
         const int seg = kind.deferred ? kSegCoarse : kSegFine;
         uint32_t *flags = kind.deferred ? plan->flags : nullptr;
-        if (plan->direct_segs[seg])
-            err = launch_direct_finalize(kind.norm, plan->tensors, plan->n_tensors,
-                                         plan->partials, plan->seg_ranges[seg], f, plan->scale,
-                                         ratio_out, norms_out, flags, s);
+        if (plan->seg_teams[seg] > 0)
+            err = launch_direct_finalize(kind.norm, plan->seg_teams[seg], plan->tensors,
+                                         plan->n_tensors, plan->partials, plan->seg_ranges[seg],
+                                         f, plan->scale, ratio_out, norms_out, flags, s);
         else
             err = launch_finalize(kind.norm, plan->tensors, plan->n_tensors, plan->partials,
                                   plan->segs[seg], plan->n_segs[seg], plan->seg_ranges[seg],

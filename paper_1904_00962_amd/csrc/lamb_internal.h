@@ -141,12 +141,26 @@ struct SegRange {
     int32_t count;
 };
 
-// Tables whose widest tensor has at most kDirectSegs segments (8.4M elements
-// in 256-element chunks) finalize in one kernel of kDirectBlock threads per
-// tensor instead of two kernels.
-constexpr int kDirectBlock = 4 * kSegBlock;
-constexpr int32_t kDirectSegs = 16;
+// A table may finalize in one kernel, a workgroup of direct_teams() teams of
+// kSegBlock threads per tensor, instead of two (a workgroup per segment, then
+// one per tensor). One kernel saves a launch, and pays for workgroups whose
+// teams idle on tensors of one segment. Two-pass steps of n one-chunk tensors
+// and one of w segments, one kernel against two: w = 1 is 2 us faster at any n
+// (12000: 36.0, 37.9); w = 2, 3, 4 even at n = 1500, 600, 400 and slower beyond
+// (w = 4, n = 12000: 78, 47.5 us); w = 5, 6 faster by 0.7 to 1.0 us up to
+// n = 160; w = 8 even; w = 12, 16 slower by 1.5 to 2.5 us at any n, since one
+// workgroup then takes several rounds of loads.
+constexpr int kDirectMaxTeams = 4;
+constexpr int kDirectBlock = kDirectMaxTeams * kSegBlock;
+constexpr int32_t kDirectSegs = 8;
+constexpr int64_t kDirectIdleTeams = 1280;
 static_assert(kDirectSegs <= 64, "one wave combines the segments' totals");
+// Teams per tensor for a table of n_tensors tensors, the widest of `widest`
+// segments; 0: two kernels.
+constexpr int32_t direct_teams(int64_t n_tensors, int64_t widest) {
+    const int32_t teams = int32_t(widest < kDirectMaxTeams ? widest : kDirectMaxTeams);
+    return widest <= kDirectSegs && (teams - 1) * n_tensors <= kDirectIdleTeams ? teams : 0;
+}
 
 // Per-chunk partial norms of x and of the update direction u (LAMB family)
 // or m_t (LARS), written once per step at a fixed slot: sums of squares (L2),
@@ -240,10 +254,10 @@ hipError_t launch_finalize(NormKind norm, const TensorDesc *tensors, int32_t n_t
                            const SegRange *ranges, Partial *seg_partials,
                            const FinalizeArgs &args, float *scale, double *ratio_out,
                            double *norms_out, uint32_t *flags, hipStream_t stream);
-// The same in one kernel, for a table whose tensors have at most kDirectSegs
-// segments each (the caller checks); `spans`: every tensor's chunk partials.
-hipError_t launch_direct_finalize(NormKind norm, const TensorDesc *tensors, int32_t n_tensors,
-                                  const Partial *partials, const SegRange *spans,
+// The same in one kernel of `teams` teams per tensor, direct_teams() of the
+// table; `spans`: every tensor's chunk partials.
+hipError_t launch_direct_finalize(NormKind norm, int32_t teams, const TensorDesc *tensors,
+                                  int32_t n_tensors, const Partial *partials, const SegRange *spans,
                                   const FinalizeArgs &args, float *scale, double *ratio_out,
                                   double *norms_out, uint32_t *flags, hipStream_t stream);
 // `check` non-null (direct mode only): also re-sum the partial norms of every
@@ -268,9 +282,10 @@ hipError_t launch_totals(NormKind norm, const Partial *partials, const SegDesc *
                          Partial *seg_partials, double *totals, uint32_t *flags,
                          const uint32_t *ctl, int32_t verdict_mode, hipStream_t stream);
 // The same in one kernel, as launch_direct_finalize.
-hipError_t launch_direct_totals(NormKind norm, const Partial *partials, const SegRange *spans,
-                                int32_t n_tensors, double *totals, uint32_t *flags,
-                                const uint32_t *ctl, int32_t verdict_mode, hipStream_t stream);
+hipError_t launch_direct_totals(NormKind norm, int32_t teams, const Partial *partials,
+                                const SegRange *spans, int32_t n_tensors, double *totals,
+                                uint32_t *flags, const uint32_t *ctl, int32_t verdict_mode,
+                                hipStream_t stream);
 // Split step, second half: per tensor the norms, phi, ratio and scale from
 // combined totals; flags[1] receives the combined verdict for a deferred
 // apply pass.

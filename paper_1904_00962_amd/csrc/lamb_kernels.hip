@@ -687,14 +687,14 @@ __global__ __launch_bounds__(kBlock) void finite_kernel(const TensorDesc *__rest
 // tensor's segment partials are combined the same way into the norms, phi,
 // trust ratio and step scale. The order never depends on timing.
 //
-// Both levels run in one kernel (kDirectBlock threads a tensor, eight segments
-// in flight) when no tensor of the table has more than kDirectSegs segments,
-// and in two kernels otherwise, same bits either way. The levels take no
-// bandwidth to speak of: they cost their launches and dependent loads.
+// Both levels run in one kernel (up to four teams of 256 threads a tensor, eight
+// segments in flight) where direct_teams() says so, and in two kernels
+// otherwise, same bits either way. The levels take no bandwidth to speak of:
+// they cost their launches, dependent loads and workgroups.
 // One kernel takes 5.9 us on BERT-Large's 1/8 share (up to 8 segments a tensor)
 // and 5.1 on ResNet-50; of two, each takes 4.7 to 5.3 (traced on BERT-Base). The
-// split step went 257.3 -> 253.9 us. Past 16 segments the loop's trips, each a
-// round of loads, would add up (a 23M-element embedding has 45 segments).
+// planless ResNet-50 step takes 177.6 us with one and 179.6 with two, the split
+// step of the share 252.4 and 252.9.
 // ---------------------------------------------------------------------------
 
 // A thread's share of one segment's partials: slots k0 + j * kSegBlock of the
@@ -732,37 +732,36 @@ __global__ __launch_bounds__(kSegBlock) void segment_kernel(const Partial *__res
 }
 
 // A tensor's combined partial norms in a fixed order, in thread 0: from its
-// segment partials, range `r` (kSegBlock threads), or, `direct`, from its chunk
-// partials, range `r` (kDirectBlock threads): waves 4 q .. 4 q + 3 fold
-// segments q, q + 4, ..., two at a time so that one latency covers both (one at
-// a time for L-infinity), and wave 0 combines the (at most kDirectSegs)
+// segment partials, range `r` (teams = 0, kSegBlock threads), or from its chunk
+// partials, range `r` (`teams` teams of kSegBlock threads): team q folds
+// segments q, q + teams, ..., two at a time so that one latency covers both (one
+// at a time for L-infinity), and wave 0 combines the (at most kDirectSegs)
 // segments' totals.
 template <int kNorm>
-__device__ Partial tensor_total(const Partial *__restrict__ partials, SegRange r, bool direct) {
+__device__ Partial tensor_total(const Partial *__restrict__ partials, SegRange r, int32_t teams) {
     constexpr int kSegWaves = kSegBlock / 64;
     __shared__ Partial total;
-    if (direct) {
-        constexpr int kTeams = kDirectBlock / kSegBlock;
+    if (teams > 0) {
         constexpr int kAtOnce = kNorm == kLinf ? 1 : 2;  // (two spill with its NaN checks)
         __shared__ Partial red[kDirectSegs][kSegWaves];
         const int n_segs = (r.count + kSegChunks - 1) / kSegChunks;
         const int k0 = int(threadIdx.x % kSegBlock);
-        for (int s = threadIdx.x / kSegBlock; s < n_segs; s += kAtOnce * kTeams) {
+        for (int s = threadIdx.x / kSegBlock; s < n_segs; s += kAtOnce * teams) {
             SegmentShare share[kAtOnce];
 #pragma unroll
             for (int h = 0; h < kAtOnce; ++h) {
-                const int32_t at = (s + h * kTeams) * kSegChunks;
+                const int32_t at = (s + h * teams) * kSegChunks;
                 const int32_t left = r.count - at;
                 share[h].load(partials + r.first + at, left < kSegChunks ? left : kSegChunks, k0);
             }
 #pragma unroll
             for (int h = 0; h < kAtOnce; ++h) {
-                if (s + h * kTeams < n_segs) {
+                if (s + h * teams < n_segs) {
                     Partial q = share[h].template combine<kNorm>();
                     q.sum_xx = wave_combine<kNorm>(q.sum_xx);
                     q.sum_uu = wave_combine<kNorm>(q.sum_uu);
                     if (threadIdx.x % 64 == 0)
-                        red[s + h * kTeams][threadIdx.x / 64 % kSegWaves] = q;
+                        red[s + h * teams][threadIdx.x / 64 % kSegWaves] = q;
                 }
             }
         }
@@ -797,11 +796,11 @@ __device__ Partial tensor_total(const Partial *__restrict__ partials, SegRange r
 template <int kNorm>
 __global__ __launch_bounds__(kDirectBlock) void finalize_kernel(
     const TensorDesc *__restrict__ tensors, const Partial *__restrict__ partials,
-    const SegRange *__restrict__ ranges, int32_t direct, FinalizeArgs a, float *__restrict__ scale,
+    const SegRange *__restrict__ ranges, int32_t teams, FinalizeArgs a, float *__restrict__ scale,
     double *__restrict__ ratio_out, double *__restrict__ norms_out, uint32_t *__restrict__ flags) {
     const int i = blockIdx.x;
     const int32_t out = tensors[i].out_index;
-    const Partial total = tensor_total<kNorm>(partials, ranges[i], direct != 0);
+    const Partial total = tensor_total<kNorm>(partials, ranges[i], teams);
     if (threadIdx.x == 0) {
         scale[i] = finish_layer<kNorm>(total, a, out, ratio_out, norms_out);
         // Deferred mode: hand the moment pass's non-finite verdict to the apply
@@ -827,11 +826,11 @@ __global__ __launch_bounds__(kDirectBlock) void finalize_kernel(
 
 template <int kNorm>
 __global__ __launch_bounds__(kDirectBlock) void totals_kernel(
-    const Partial *__restrict__ partials, const SegRange *__restrict__ ranges, int32_t direct,
+    const Partial *__restrict__ partials, const SegRange *__restrict__ ranges, int32_t teams,
     int32_t n_tensors, double *__restrict__ totals, uint32_t *__restrict__ flags,
     const uint32_t *__restrict__ ctl, int32_t verdict_mode) {
     const int i = blockIdx.x;
-    const Partial total = tensor_total<kNorm>(partials, ranges[i], direct != 0);
+    const Partial total = tensor_total<kNorm>(partials, ranges[i], teams);
     if (threadIdx.x == 0) {
         totals[2 * i] = total.sum_xx;
         totals[2 * i + 1] = total.sum_uu;
@@ -1964,32 +1963,33 @@ hipError_t launch_segments(NormKind norm, const Partial *partials, const SegDesc
     return hipLaunchKernel(fn, dim3(n_segs), dim3(kSegBlock), params, 0, stream);
 }
 
-// The per-tensor level over segment partials or, `direct`, chunk partials.
+// The per-tensor level over segment partials or, with `teams` teams a tensor,
+// chunk partials.
 hipError_t launch_finalize_level(NormKind norm, const TensorDesc *tensors, int32_t n_tensors,
-                                 const Partial *partials, const SegRange *ranges, int32_t direct,
+                                 const Partial *partials, const SegRange *ranges, int32_t teams,
                                  const FinalizeArgs &args, float *scale, double *ratio_out,
                                  double *norms_out, uint32_t *flags, hipStream_t stream) {
     FinalizeArgs a = args;
-    void *params[] = {&tensors, &partials,  &ranges,    &direct, &a,
+    void *params[] = {&tensors, &partials,  &ranges,    &teams, &a,
                       &scale,   &ratio_out, &norms_out, &flags};
     const void *fn = norm == kL1     ? reinterpret_cast<const void *>(&finalize_kernel<kL1>)
                      : norm == kLinf ? reinterpret_cast<const void *>(&finalize_kernel<kLinf>)
                                      : reinterpret_cast<const void *>(&finalize_kernel<kL2>);
-    return hipLaunchKernel(fn, dim3(n_tensors), dim3(direct ? kDirectBlock : kSegBlock), params,
-                           0, stream);
+    return hipLaunchKernel(fn, dim3(n_tensors), dim3(teams > 0 ? teams * kSegBlock : kSegBlock),
+                           params, 0, stream);
 }
 
 hipError_t launch_totals_level(NormKind norm, const Partial *partials, const SegRange *ranges,
-                               int32_t direct, int32_t n_tensors, double *totals,
+                               int32_t teams, int32_t n_tensors, double *totals,
                                uint32_t *flags, const uint32_t *ctl, int32_t verdict_mode,
                                hipStream_t stream) {
-    void *params[] = {&partials, &ranges, &direct, &n_tensors,
+    void *params[] = {&partials, &ranges, &teams, &n_tensors,
                       &totals,   &flags,  &ctl,    &verdict_mode};
     const void *fn = norm == kL1     ? reinterpret_cast<const void *>(&totals_kernel<kL1>)
                      : norm == kLinf ? reinterpret_cast<const void *>(&totals_kernel<kLinf>)
                                      : reinterpret_cast<const void *>(&totals_kernel<kL2>);
-    return hipLaunchKernel(fn, dim3(n_tensors), dim3(direct ? kDirectBlock : kSegBlock), params,
-                           0, stream);
+    return hipLaunchKernel(fn, dim3(n_tensors), dim3(teams > 0 ? teams * kSegBlock : kSegBlock),
+                           params, 0, stream);
 }
 
 bool totals_verdict_ok(int32_t mode, const uint32_t *ctl) {
@@ -2010,11 +2010,13 @@ hipError_t launch_finalize(NormKind norm, const TensorDesc *tensors, int32_t n_t
                                  ratio_out, norms_out, flags, stream);
 }
 
-hipError_t launch_direct_finalize(NormKind norm, const TensorDesc *tensors, int32_t n_tensors,
-                                  const Partial *partials, const SegRange *spans,
+hipError_t launch_direct_finalize(NormKind norm, int32_t teams, const TensorDesc *tensors,
+                                  int32_t n_tensors, const Partial *partials, const SegRange *spans,
                                   const FinalizeArgs &args, float *scale, double *ratio_out,
                                   double *norms_out, uint32_t *flags, hipStream_t stream) {
-    return launch_finalize_level(norm, tensors, n_tensors, partials, spans, 1, args, scale,
+    if (teams < 1 || teams > kDirectMaxTeams)
+        return hipErrorInvalidValue;
+    return launch_finalize_level(norm, tensors, n_tensors, partials, spans, teams, args, scale,
                                  ratio_out, norms_out, flags, stream);
 }
 
@@ -2031,12 +2033,13 @@ hipError_t launch_totals(NormKind norm, const Partial *partials, const SegDesc *
                                verdict_mode, stream);
 }
 
-hipError_t launch_direct_totals(NormKind norm, const Partial *partials, const SegRange *spans,
-                                int32_t n_tensors, double *totals, uint32_t *flags,
-                                const uint32_t *ctl, int32_t verdict_mode, hipStream_t stream) {
-    if (!totals_verdict_ok(verdict_mode, ctl))
+hipError_t launch_direct_totals(NormKind norm, int32_t teams, const Partial *partials,
+                                const SegRange *spans, int32_t n_tensors, double *totals,
+                                uint32_t *flags, const uint32_t *ctl, int32_t verdict_mode,
+                                hipStream_t stream) {
+    if (!totals_verdict_ok(verdict_mode, ctl) || teams < 1 || teams > kDirectMaxTeams)
         return hipErrorInvalidValue;
-    return launch_totals_level(norm, partials, spans, 1, n_tensors, totals, flags, ctl,
+    return launch_totals_level(norm, partials, spans, teams, n_tensors, totals, flags, ctl,
                                verdict_mode, stream);
 }
 

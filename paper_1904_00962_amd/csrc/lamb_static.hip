@@ -271,6 +271,7 @@ lamb_status lamb_step_static(const lamb_tensor *tensors, int32_t n_tensors, int3
     st = check_hparams(nullptr, hp, nonfinite_out);
     if (st != LAMB_OK)
         return st;
+    const StepKind kind = step_kind(*hp, g_dtype);
     const bool needs_v = hp->variant != LAMB_VARIANT_LARS;
     {
         std::lock_guard<std::mutex> lock(g_static_mutex);
@@ -281,11 +282,12 @@ lamb_status lamb_step_static(const lamb_tensor *tensors, int32_t n_tensors, int3
     }
     const int32_t coarse =
         int32_t(std::min<int64_t>(int64_t(chunk) * kCoarseFactor, kMaxChunkElems));
-    int64_t n_chunks = 0, n_coarse = 0, largest = 0;
+    const int64_t seg_elems = int64_t(kSegChunks) * (kind.deferred ? coarse : chunk);
+    int64_t n_chunks = 0, n_coarse = 0, widest = 0;
     for (int32_t i = 0; i < n_tensors; ++i) {
         n_chunks += (tensors[i].numel + chunk - 1) / chunk;
         n_coarse += (tensors[i].numel + coarse - 1) / coarse;
-        largest = std::max(largest, tensors[i].numel);
+        widest = std::max(widest, (tensors[i].numel + seg_elems - 1) / seg_elems);
         if (n_chunks > kStaticMaxChunks)
             return fail(LAMB_EINVAL, "more than %d chunks of %d elements (at most %d chunks "
                         "without a plan); raise chunk_elems", kStaticMaxChunks, chunk,
@@ -293,7 +295,6 @@ lamb_status lamb_step_static(const lamb_tensor *tensors, int32_t n_tensors, int3
     }
     if (n_coarse > kStaticMaxCoarse)
         return fail(LAMB_EINVAL, "more than %d coarse chunks", kStaticMaxCoarse);
-    const StepKind kind = step_kind(*hp, g_dtype);
     StepArgs a = step_args(*hp);
     const FinalizeArgs f = finalize_args(*hp);
     char *base = nullptr;
@@ -302,8 +303,7 @@ lamb_status lamb_step_static(const lamb_tensor *tensors, int32_t n_tensors, int3
         return fail_hip(err, "looking up the static device array");
     const StaticTables t = static_tables(base);
     const int seg = kind.deferred ? 1 : 0;
-    const bool direct =
-        largest <= int64_t(kDirectSegs) * kSegChunks * (kind.deferred ? coarse : chunk);
+    const int32_t teams = direct_teams(n_tensors, widest);
     hipStream_t s = static_cast<hipStream_t>(stream);
     // The tables, batch by batch, as kernel arguments.
     TableBatch b;
@@ -329,7 +329,7 @@ lamb_status lamb_step_static(const lamb_tensor *tensors, int32_t n_tensors, int3
         first_seg += (nc + kSegChunks - 1) / kSegChunks;
         first_cseg += (ncc + kSegChunks - 1) / kSegChunks;
         if (b.count == kTableBatch || i == n_tensors - 1) {
-            err = launch_table(b, t, direct, s);
+            err = launch_table(b, t, teams > 0, s);
             if (err != hipSuccess)
                 return fail_hip(err, "launching the table kernel");
             b.count = 0;
@@ -343,9 +343,9 @@ lamb_status lamb_step_static(const lamb_tensor *tensors, int32_t n_tensors, int3
     if (err != hipSuccess)
         return fail_hip(err, "launching the moment kernel");
     uint32_t *flags = kind.deferred ? t.flags : nullptr;
-    if (direct)
-        err = launch_direct_finalize(kind.norm, t.tensors, n_tensors, t.partials, t.ranges[seg],
-                                     f, t.scale, ratio_out, norms_out, flags, s);
+    if (teams > 0)
+        err = launch_direct_finalize(kind.norm, teams, t.tensors, n_tensors, t.partials,
+                                     t.ranges[seg], f, t.scale, ratio_out, norms_out, flags, s);
     else
         err = launch_finalize(kind.norm, t.tensors, n_tensors, t.partials, t.segs[seg],
                               kind.deferred ? first_cseg : first_seg, t.ranges[seg],

@@ -41,14 +41,14 @@ hipError_t launch_finite(bool, const TensorDesc *, const ChunkDesc *, int32_t, u
     return hipErrorNotSupported;
 }
 
-hipError_t launch_direct_finalize(NormKind, const TensorDesc *, int32_t, const Partial *,
-                                  const SegRange *, const FinalizeArgs &, float *, double *,
-                                  double *, uint32_t *, hipStream_t) {
+hipError_t launch_direct_finalize(NormKind, int32_t, const TensorDesc *, int32_t,
+                                  const Partial *, const SegRange *, const FinalizeArgs &,
+                                  float *, double *, double *, uint32_t *, hipStream_t) {
     return hipErrorNotSupported;
 }
 
-hipError_t launch_direct_totals(NormKind, const Partial *, const SegRange *, int32_t, double *,
-                                uint32_t *, const uint32_t *, int32_t, hipStream_t) {
+hipError_t launch_direct_totals(NormKind, int32_t, const Partial *, const SegRange *, int32_t,
+                                double *, uint32_t *, const uint32_t *, int32_t, hipStream_t) {
     return hipErrorNotSupported;
 }
 

@@ -1,8 +1,9 @@
-"""The finalize in one kernel (no tensor of more than sixteen segments) and in
-two, at the sizes where a segment or the one-kernel range ends: the same
-tensors alone and beside a wider one, each against the oracle and against each
-other bit for bit (the order of every sum is the same). And the planless
-step's table, at the tensor counts where a batch of it ends."""
+"""The finalize in one kernel (no tensor of more than eight segments, and not
+too many tensors) and in two, at the sizes where a segment or the one-kernel
+range ends: the same tensors alone and beside a wider one, or among thousands,
+each against the oracle and against each other bit for bit (the order of every
+sum is the same). And the planless step's table, at the tensor counts where a
+batch of it ends."""
 
 import numpy as np
 import pytest
@@ -15,8 +16,8 @@ pytestmark = pytest.mark.gpu
 CHUNK = 8
 SEG = 2048 * CHUNK           # elements of a segment
 SIZES = [1, 7, 8, 255 * CHUNK, SEG - 1, SEG, SEG + 1, 4 * SEG, 4 * SEG + 1, 5 * SEG + 9,
-         16 * SEG - 8, 16 * SEG]
-WIDER = 16 * SEG + 1
+         8 * SEG - 8, 8 * SEG]
+WIDER = 8 * SEG + 1
 
 
 @pytest.mark.parametrize("variant,norm,skip", [("lamb", "l2", 0), ("lamb", "l1", 1),
@@ -53,6 +54,36 @@ def test_one_kernel_equals_two(call, variant, norm, skip):
         pair.close()
     for a, b in zip(*states):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("norm", ["l2", "linf"])
+def test_any_number_of_tensors(norm):
+    """Tensors of one segment among a few, in one kernel of four teams a tensor;
+    among thousands, in one kernel of one team; beside one of two segments, in
+    two kernels."""
+    torch = H.torch_cuda()
+    rng = np.random.default_rng(6)
+    first = [1, 9, 2047 * CHUNK, SEG]
+    xs, states = [], []
+    for tail in ([300, 4 * SEG], [7] * 3000, [7] * 3000 + [SEG + 1]):
+        sizes = first + tail
+        while len(xs) < len(first):
+            xs.append((rng.standard_normal(first[len(xs)]) * 0.05).astype(np.float32))
+        here = xs + [(rng.standard_normal(s) * 0.05).astype(np.float32) for s in tail]
+        subset = list(range(len(first))) + [len(sizes) - 2, len(sizes) - 1]
+        pair = H.Pair(here, [True] * len(sizes), "f32", "lamb", chunk_elems=CHUNK,
+                      oracle_subset=subset, path="two-pass")
+        hg = pair.set_grads([torch.full((s,), 1e-3) for s in sizes])
+        hp = _lib.lamb_hparams_init("lamb", step=1, lr=1e-2, norm=norm)
+        tol = pair.ratio_tolerances(hp, hg)
+        pair.compare(H.step_ex_both(pair, hp, hg), "%s, %d tensors" % (norm, len(sizes)), tol)
+        n = len(first)
+        states.append([s.clone() for s in pair.X[:n] + pair.M[:n]] +
+                      [pair.ratio[:n].clone(), pair.norms[:2 * n].clone()])
+        pair.close()
+    for other in states[1:]:
+        for a, b in zip(states[0], other):
+            assert torch.equal(a, b)
 
 
 @pytest.mark.parametrize("n", [1, 81, 82, 83, 165])
