@@ -15,6 +15,7 @@ from paper_1904_00962_amd import build
 KERNEL_SOURCES = [os.path.join(build.CSRC, name)
                   for name in ("lamb_kernels.hip", "lamb_static.hip")]
 LDS_PER_CU = 160 * 1024
+SINGLE_PASS = ("fused_kernel", "quick_kernel")
 
 
 @pytest.fixture(scope="module")
@@ -45,7 +46,8 @@ def kernels(tmp_path_factory):
 def test_every_kernel_variant_was_found(kernels):
     names = list(kernels)
     # 4 algorithms x 2 gradient dtypes x 3 norms, in both tile shapes
-    assert sum("fused_kernel" in n for n in names) == 48
+    for kind in SINGLE_PASS:
+        assert sum(kind in n for n in names) == 48, kind
     # 4 algorithms x 2 gradient dtypes x (direct, deferred) x 3 norms
     assert sum("moments_kernel" in n for n in names) == 48
     # 4 algorithms x 2 gradient dtypes x (deferred, direct, direct with the
@@ -54,7 +56,10 @@ def test_every_kernel_variant_was_found(kernels):
     for kind in ("segment_kernel", "finalize_kernel", "totals_kernel", "scale_kernel"):
         assert sum(kind in n for n in names) == 3, kind
     assert sum("finite_kernel" in n for n in names) == 2
-    assert sum("table_kernel" in n for n in names) == 1
+    for kind in ("table_kernel", "tile_copies_kernel"):
+        assert sum(kind in n for n in names) == 1, kind
+    # and no other kernel, whose resources nothing here would bound
+    assert len(names) == 2 * 48 + 48 + 40 + 4 * 3 + 2 + 2
 
 
 def test_no_kernel_spills(kernels):
@@ -64,7 +69,7 @@ def test_no_kernel_spills(kernels):
 
 def test_single_pass_fits_four_workgroups_per_cu(kernels):
     for name, k in kernels.items():
-        if "fused_kernel" not in name:
+        if not any(kind in name for kind in SINGLE_PASS):
             continue
         assert k["vgpr"] <= 128, (name, k)
         assert 4 * k["lds"] <= LDS_PER_CU, (name, k)
