@@ -268,10 +268,10 @@ LAMB_API lamb_status lamb_plan_tiles(const lamb_plan *plan, int32_t *tiles_per_t
 
 /*
  * Wait for `stream` and report whether a single-pass step of the plan gave
- * up a wait (a layer's tiles were not all resident within about a second:
+ * up a wait (a layer's tiles were not all resident within a second or two:
  * 2^22 polls, or the count in the environment variable
  * LAMB_MI355X_SPIN_LIMIT when lamb_plan_create ran, which tests use to
- * exercise this path; a value that is not a positive integer makes
+ * exercise this path, and twice the count for waits that poll faster; a value that is not a positive integer makes
  * lamb_plan_create fail with LAMB_EINVAL, and values above 2^30 count as
  * 2^30).
  * That step's state is then undefined (tiles that finished reading had

@@ -55,8 +55,9 @@ constexpr int kFusedBlocksPerCu = kFusedWaves * 4 / kWaves;  // 4 SIMDs per CU
 // parameters 2% each (3 to 9 rounds), BERT-Base 0.8% slower (fp32, 11 rounds),
 // GPT shapes of 120M and 1.5B 1.1-3% slower, BERT-Large 2.4% slower (37 rounds).
 constexpr int32_t kQuickRounds = 10;
-// Polls before a single-pass wait gives up (about a second); a plan reads an
-// override from the environment variable LAMB_MI355X_SPIN_LIMIT.
+// Polls before a single-pass wait gives up (1.5 s at 0.35 us a poll); a plan
+// reads an override from the environment variable LAMB_MI355X_SPIN_LIMIT, at
+// most 2^30 (twice that still fits the 32-bit count of an eager wait).
 constexpr uint32_t kDefaultSpinLimit = 1u << 22;
 
 // Synchronisation words of the single-pass path (per plan).

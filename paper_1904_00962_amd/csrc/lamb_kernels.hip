@@ -902,15 +902,20 @@ __global__ __launch_bounds__(kSegBlock) void scale_kernel(
 // the next step; the last workgroup to finish advances the epoch (a step
 // skipped for a non-finite gradient touches no slot and leaves it). Nothing
 // depends on a host counter, so a captured graph replays correctly.
-// Every wait is bounded: after StepArgs::spin_limit polls, or once another
-// workgroup has given up, a workgroup raises the sticky fault word and
-// abandons the step, and every later step of the plan does nothing.
+// Every wait is bounded: after StepArgs::spin_limit polls (kEagerPolls times as
+// many of an eager wait, whose polls are shorter), or once another workgroup has
+// given up, a workgroup raises the sticky fault word and abandons the step, and
+// every later step of the plan does nothing.
 // ---------------------------------------------------------------------------
 
 // s_sleep argument between polls (units of 64 clocks): 512 clocks beat 128,
 // 256 and 1024 by 0.3-0.6% on BERT-Large.
 constexpr int kPollSleep = 8;
 constexpr int kEagerSleep = 2;  // of an eager wait
+// An eager wait may poll this often for each poll of another one, so that it
+// gives up no sooner: a poll takes 0.19-0.23 us (most of it the load) against
+// 0.35, at 1 to 1024 waiting workgroups.
+constexpr uint32_t kEagerPolls = 2;
 // A workgroup that waits for its layer's scale drops its waves to the lowest
 // issue priority (s_setprio 0) and raises them (to 3) once the scale is
 // known, so that waves with reads and writes to issue go first (1.2-1.4%
@@ -966,7 +971,7 @@ __device__ uint64_t slot_wait(const uint64_t *p, uint32_t *ctl, uint32_t limit) 
         const uint64_t w = slot_load(p);
         if (w != kEmptySlot)
             return w;
-        if (gives_up(k, ctl, limit))
+        if (gives_up(k, ctl, kSleep == kEagerSleep ? kEagerPolls * limit : limit))
             return kEmptySlot;
         __builtin_amdgcn_s_sleep(kSleep);
     }
@@ -1226,7 +1231,7 @@ __device__ __forceinline__ bool gather_team(const uint64_t *slots_x, const uint6
                 all = all && wx[q] != kEmptySlot && wu[q] != kEmptySlot;
             if (all)
                 break;
-            if (gives_up(polls, ctl, limit))
+            if (gives_up(polls, ctl, kEagerPolls * limit))
                 return false;
             __builtin_amdgcn_s_sleep(kEagerSleep);
         }
@@ -1586,7 +1591,6 @@ void quick_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
                   StepArgs a, FinalizeArgs f, double *__restrict__ ratio_out,
                   double *__restrict__ norms_out, const double *__restrict__ ext_totals,
                   float *__restrict__ ext_scale, uint64_t *__restrict__ trace) {
-    constexpr bool kV = kHasSecondMoment<kAlgo>;
     constexpr int kUnrollF = kFusedUnroll<kAlgo>;
     __shared__ uint32_t sh_epoch, sh_fault, sh_skip, sh_stop;
     __shared__ float sh_scale;

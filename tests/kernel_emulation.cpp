@@ -1,7 +1,8 @@
 // The single-pass kernels on the CPU, from their own source, waves in either
 // order (kernel_emulation.h): layers one after the other in the rounds of one
 // plan must come out bit for bit as each of them alone in a plan of one round.
-// Prints what differs; the exit status is the number of differing layers.
+// And a wait that is not eager and one that is give up after the same time.
+// Prints what differs; the exit status is 0 when nothing does.
 #include "kernel_emulation.h"
 
 #include "lamb_kernels.hip"
@@ -59,6 +60,7 @@ struct Call {
     uint32_t *ctl, *flags;
     double *ratios;
     bool quick;
+    uint32_t spin_limit = 1u << 30;
 };
 
 template <int kAlgo, int kGroups>
@@ -74,7 +76,7 @@ void kernel_body(void *p) {
     a.eps = 0.0f;
     a.weight_decay = 0.01f;
     a.grad_scale = 1.0f;
-    a.spin_limit = 1u << 30;
+    a.spin_limit = c.spin_limit;
     const FinalizeArgs f{0.01, 0.0, 10.0, 1.0};
     const int32_t n = int32_t(c.tiles->size());
     if (c.quick)
@@ -135,6 +137,51 @@ int compare(const char *name, uint32_t grid, const std::vector<int> &numels) {
     return bad;
 }
 
+// A wait that nothing ends, alone on the device: a layer of two tiles of which
+// only tile `index` runs, in a plan of one round or of two. Returns its sleeps,
+// or 0 when it did not give up.
+uint64_t sleeps_of_a_wait(bool quick, bool one_round, uint32_t index, uint32_t limit) {
+    std::vector<Layer> layers;
+    layers.emplace_back(8192 + 4096, 1u);
+    layers.emplace_back(8192 + 4096, 2u);
+    std::vector<TileDesc> tiles;
+    add_tiles(&tiles, &layers[0], 8, 0);
+    if (!one_round)
+        add_tiles(&tiles, &layers[1], 8, 1);
+    std::vector<uint64_t> slots(6 * tiles.size(), kEmptySlot);
+    std::vector<uint32_t> ctl(64, 0), flags(64, 0);
+    std::vector<double> ratios(2, -1.0);
+    Call c{&tiles, slots.data(), ctl.data(), flags.data(), ratios.data(), quick, limit};
+    uint64_t n = 0;
+    std::thread([&] {
+        emulation::run_workgroup(index, 2, uint32_t(kBlock), false, &kernel_body<kLamb, 8>, &c);
+        n = emulation::sleeps;
+    }).join();
+    return ctl[kCtlFault] != 0 ? n : 0;
+}
+
+// An eager wait's polls are shorter than another wait's, by up to 1.85 times
+// (0.19 to 0.23 us, 0.35): it may not give up after fewer than twice as many,
+// or a step that used to wait a busy device out would be abandoned.
+int check_patience() {
+    constexpr uint32_t kLimit = 600;
+    int bad = 0;
+    auto expect = [&](const char *what, uint64_t got, uint64_t polls) {
+        if (got != polls - 1) {  // (a poll that finds the limit reached does not sleep)
+            printf("%s gives up after %llu polls, not %llu\n", what,
+                   static_cast<unsigned long long>(got + 1), static_cast<unsigned long long>(polls));
+            ++bad;
+        }
+    };
+    expect("quick_kernel, several rounds", sleeps_of_a_wait(true, false, 1, kLimit), kLimit);
+    expect("fused_kernel, a member", sleeps_of_a_wait(false, true, 1, kLimit), kLimit);
+    expect("quick_kernel, one round", sleeps_of_a_wait(true, true, 1, kLimit), 2 * kLimit);
+    expect("quick_kernel, one round, the leader", sleeps_of_a_wait(true, true, 0, kLimit),
+           2 * kLimit);
+    expect("fused_kernel, an eager leader", sleeps_of_a_wait(false, true, 0, kLimit), 2 * kLimit);
+    return bad;
+}
+
 }  // namespace
 
 int main() {
@@ -151,5 +198,8 @@ int main() {
                              {8192 + 41, 8192 + 1024 + 803, 8192 + 4097, 16384 - 3, 8192 + 1021});
     if (bad == 0)
         printf("all layers agree\n");
-    return bad != 0;
+    const int impatient = check_patience();
+    if (impatient == 0)
+        printf("all waits are as patient\n");
+    return bad + impatient != 0;
 }

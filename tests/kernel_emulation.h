@@ -70,6 +70,7 @@ struct Workgroup {
 
 inline thread_local Workgroup *group = nullptr;
 inline thread_local Dim thread_index;
+inline thread_local uint64_t sleeps = 0;  // s_sleep calls of the workgroup's lanes
 
 inline void lane_main() {
     Workgroup *g = group;
@@ -214,7 +215,7 @@ inline uint32_t atomicOr(uint32_t *p, uint32_t v) { return __atomic_fetch_or(p, 
 #define __builtin_amdgcn_s_setprio(p) ((void)0)
 #define __builtin_amdgcn_sched_barrier(m) ((void)0)
 #define __builtin_amdgcn_s_memrealtime() uint64_t(0)
-#define __builtin_amdgcn_s_sleep(n) ((void)sched_yield())
+#define __builtin_amdgcn_s_sleep(n) ((void)++emulation::sleeps, (void)sched_yield())
 
 // quad_perm (controls below 0x100), row_mirror, row_half_mirror
 inline int __builtin_amdgcn_mov_dpp(int v, int control, int, int, bool) {

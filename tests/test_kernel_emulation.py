@@ -16,7 +16,9 @@ from paper_1904_00962_amd import build
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
-def test_no_wave_overtakes_another(tmp_path):
+@pytest.fixture(scope="module")
+def output(tmp_path_factory):
+    tmp_path = tmp_path_factory.mktemp("emulation")
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     clang = shutil.which("amdclang++") or os.path.join(rocm, "llvm", "bin", "clang++")
     if not os.path.exists(clang):
@@ -32,5 +34,15 @@ def test_no_wave_overtakes_another(tmp_path):
                        capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr[-2000:]
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
-    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
-    assert "all layers agree" in r.stdout
+    return r.stdout + r.stderr
+
+
+def test_no_wave_overtakes_another(output):
+    assert "all layers agree" in output, output[-2000:]
+
+
+def test_an_eager_wait_gives_up_no_sooner(output):
+    """A give-up counts polls, and an eager wait's are shorter: it gets more of
+    them, so that a layer whose tiles are late on a busy device is waited for as
+    long in a plan of one round as in any other."""
+    assert "all waits are as patient" in output, output[-2000:]
