@@ -93,3 +93,148 @@ def test_ragged_layers_in_successive_rounds(path, n, quick):
     assert all(r <= 1 for _, r in parts)
     for k, a in enumerate(whole):
         assert torch.equal(a, torch.cat([p[0][k] for p in parts]))
+
+
+class _Copies:
+    """A bf16 copy of every layer: the SIZES layers' between guard bands of 8
+    elements, the fillers' in slots of 64."""
+
+    GUARD = -3.0
+
+    def __init__(self, pair):
+        torch = H.torch_cuda()
+        sizes = [x.numel() for x in pair.X]
+        n = len(SIZES)
+        self.bands = [torch.full((s + 16,), self.GUARD, dtype=torch.bfloat16, device="cuda")
+                      for s in sizes[:n]]
+        self.fill = torch.full((max(1, len(sizes) - n), 64), self.GUARD, dtype=torch.bfloat16,
+                               device="cuda")
+        self.pair = pair
+        _lib.lamb_plan_set_bf16_copies(
+            pair.plan, [b.data_ptr() + 16 for b in self.bands] +
+            [self.fill.data_ptr() + 128 * k for k in range(len(sizes) - n)])
+
+    def check(self):
+        """Every copy is its x rounded; nothing around it was written."""
+        torch = H.torch_cuda()
+        for x, b in zip(self.pair.X, self.bands):
+            assert torch.equal(b[8:-8], x.to(torch.bfloat16)), x.numel()
+            assert bool((b[:8] == self.GUARD).all()) and bool((b[-8:] == self.GUARD).all())
+        want = torch.full_like(self.fill, self.GUARD)
+        for k, x in enumerate(self.pair.X[len(SIZES):]):
+            want[k, :x.numel()] = x.to(torch.bfloat16)
+        assert torch.equal(self.fill, want)
+
+
+def _plan_state(pair):
+    return [t.clone() for t in pair.X + pair.M + (pair.V if pair.V is not None else [])]
+
+
+def _equal(a, b):
+    return len(a) == len(b) and all(H.torch_cuda().equal(p, q) for p, q in zip(a, b))
+
+
+def _options_inputs(long, seed):
+    rng = np.random.default_rng(seed)
+    sizes = SIZES + ([1 + 37 * k % 61 for k in range(FILLERS)] if long else [])
+    xs = [(rng.standard_normal(s) * 0.05).astype(np.float32) for s in sizes]
+    grads = [[(rng.standard_normal(s) * 1e-3 + 2e-3).astype(np.float32) for s in sizes]
+             for _ in range(3)]
+    return sizes, xs, grads, [k % 2 == 0 for k in range(len(sizes))]
+
+
+@pytest.mark.parametrize("long", [False, True])
+@pytest.mark.parametrize("captured", [False, True])
+@pytest.mark.parametrize("path,variant,g_dtype", [("auto", "lamb", "bf16"), ("wide", "lars", "f32"),
+                                                  ("wide", "nn-lamb", "bf16")])
+def test_copies_skips_and_replays(path, variant, g_dtype, captured, long):
+    """Both kernels with bf16 copies and skip_nonfinite, eager or replayed from a
+    graph: a step, a step skipped for a NaN in one layer (the last of the plan,
+    then the first), a step, a step. A skipped one reports it and writes nothing;
+    the others match the oracle, and each copy is its layer's x."""
+    torch = H.torch_cuda()
+    algo = "lars" if variant == "lars" else "lamb"
+    n = len(SIZES)
+    sizes, xs, grads, wd = _options_inputs(long, 91)
+    # (replays repeat one step number)
+    hp = _lib.lamb_hparams_init(variant, step=2, lr=1e-2, skip_nonfinite=1)
+    pair = H.Pair(xs, wd, g_dtype, algo, oracle_subset=range(n), path=path)
+    try:
+        assert (_rounds(pair.plan, sizes) > QUICK_ROUNDS) == long
+        copies = _Copies(pair)
+        verdict = torch.full((1,), 7, dtype=torch.int32, device="cuda")
+
+        def step():
+            _lib.lamb_step_ex(pair.plan, hp, torch.cuda.current_stream().cuda_stream,
+                              pair.ratio.data_ptr(), pair.norms.data_ptr(), verdict.data_ptr())
+
+        graph = None
+        for t, nan_layer in enumerate([None, len(sizes) - 1, None, 0, None]):
+            gs = [torch.from_numpy(g.copy()) for g in grads[t % 3]]
+            if nan_layer is not None:
+                gs[nan_layer][-1] = float("nan")
+            hg = pair.set_grads(gs)
+            tol = None if nan_layer is not None else pair.ratio_tolerances(hp, hg)
+            before = _plan_state(pair)
+            torch.cuda.synchronize()
+            if captured and t == 1:
+                side = torch.cuda.Stream()
+                side.wait_stream(torch.cuda.current_stream())
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph, stream=side):
+                    step()
+                torch.cuda.synchronize()
+            if graph is not None:
+                graph.replay()
+            else:
+                step()
+            torch.cuda.synchronize()
+            label = "%s %s t=%d" % (variant, "long" if long else "short", t)
+            if nan_layer is not None:
+                assert int(verdict) == 1, label
+                assert _equal(before, _plan_state(pair)), label
+            else:
+                assert int(verdict) == 0, label
+                pair.compare(H.step_ex_both_oracle(pair, hp, hg), label, tol)
+            copies.check()
+        _lib.lamb_plan_check(pair.plan)
+    finally:
+        pair.close()
+
+
+@pytest.mark.parametrize("long", [False, True])
+@pytest.mark.parametrize("path", ["auto", "wide"])
+def test_abandoned_wait_on_both_kernels(path, long, monkeypatch):
+    """With a budget of one poll a wait gives up (every workgroup still exits):
+    the plan reports it and its later steps write nothing, the copies included;
+    a plan with the normal budget steps on."""
+    torch = H.torch_cuda()
+    n = len(SIZES)
+    sizes, xs, grads, wd = _options_inputs(long, 92)
+    hp = _lib.lamb_hparams_init("lamb", step=1, lr=1e-2)
+    out = lambda p: (p.ratio.data_ptr(), p.norms.data_ptr())  # noqa: E731
+    monkeypatch.setenv("LAMB_MI355X_SPIN_LIMIT", "1")
+    pair = H.Pair(xs, wd, "f32", "lamb", oracle_subset=range(n), path=path)
+    monkeypatch.delenv("LAMB_MI355X_SPIN_LIMIT")
+    try:
+        assert (_rounds(pair.plan, sizes) > QUICK_ROUNDS) == long
+        copies = _Copies(pair)
+        pair.set_grads([torch.from_numpy(g) for g in grads[0]])
+        _lib.lamb_step_ex(pair.plan, hp, 0, *out(pair))
+        with pytest.raises(_lib.LambError) as e:
+            _lib.lamb_plan_check(pair.plan)
+        assert e.value.status == _lib.LAMB_ESYNC
+        before = _plan_state(pair) + [b.clone() for b in copies.bands + [copies.fill]]
+        _lib.lamb_step_ex(pair.plan, hp, 0, *out(pair))
+        torch.cuda.synchronize()
+        assert _equal(before, _plan_state(pair) + copies.bands + [copies.fill])
+    finally:
+        pair.close()
+    pair = H.Pair(xs, wd, "f32", "lamb", oracle_subset=range(n), path=path)
+    try:
+        hg = pair.set_grads([torch.from_numpy(g) for g in grads[0]])
+        tol = pair.ratio_tolerances(hp, hg)
+        pair.compare(H.step_ex_both(pair, hp, hg), "after a give-up", tol)
+        _lib.lamb_plan_check(pair.plan)
+    finally:
+        pair.close()
