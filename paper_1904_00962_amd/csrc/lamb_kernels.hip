@@ -914,7 +914,10 @@ constexpr int kPollSleep = 8;
 constexpr int kEagerSleep = 2;  // of an eager wait
 // An eager wait may poll this often for each poll of another one, so that it
 // gives up no sooner: a poll takes 0.19-0.23 us (most of it the load) against
-// 0.35, at 1 to 1024 waiting workgroups.
+// 0.35, at 1 to 1024 waiting workgroups. quick_kernel, all of whose waits are
+// eager in a plan of one round and none in another, gets its limit multiplied
+// already (by launch_single_pass: a multiplication at each of its waits made
+// 500 one-tile layers 1.7% slower).
 constexpr uint32_t kEagerPolls = 2;
 // A workgroup that waits for its layer's scale drops its waves to the lowest
 // issue priority (s_setprio 0) and raises them (to 3) once the scale is
@@ -971,7 +974,7 @@ __device__ uint64_t slot_wait(const uint64_t *p, uint32_t *ctl, uint32_t limit) 
         const uint64_t w = slot_load(p);
         if (w != kEmptySlot)
             return w;
-        if (gives_up(k, ctl, kSleep == kEagerSleep ? kEagerPolls * limit : limit))
+        if (gives_up(k, ctl, limit))
             return kEmptySlot;
         __builtin_amdgcn_s_sleep(kSleep);
     }
@@ -1231,7 +1234,7 @@ __device__ __forceinline__ bool gather_team(const uint64_t *slots_x, const uint6
                 all = all && wx[q] != kEmptySlot && wu[q] != kEmptySlot;
             if (all)
                 break;
-            if (gives_up(polls, ctl, kEagerPolls * limit))
+            if (gives_up(polls, ctl, limit))
                 return false;
             __builtin_amdgcn_s_sleep(kEagerSleep);
         }
@@ -1476,8 +1479,10 @@ void fused_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
                 // than half a round: its scale should come as soon as it can
                 // (GPT-2 1.5B 0.4% faster; BERT-Large's layers take half a round,
                 // and faster scales only drive its workgroups apart: 0.4% slower).
-                if (!gather_team<kNorm>(cur_x, cur_u, first, team, 2 * team > grid, ctl,
-                                        a.spin_limit, ax, au))
+                const bool eager = 2 * team > grid;
+                if (!gather_team<kNorm>(cur_x, cur_u, first, team, eager, ctl,
+                                        eager ? kEagerPolls * a.spin_limit : a.spin_limit, ax,
+                                        au))
                     give_up = 1;
                 block_combine<kNorm, kWaves>(ax, au, &sh_layer);
                 give_up = __syncthreads_or(give_up);
@@ -2071,6 +2076,8 @@ hipError_t launch_single_pass(const StepKind &kind, int groups, const TileDesc *
     if (!fn)
         return hipErrorInvalidValue;
     StepArgs a = args;
+    if (n_tiles <= grid)
+        a.spin_limit *= kEagerPolls;
     FinalizeArgs f = fargs;
     int32_t guard = guarded ? 1 : 0;
     void *params[] = {&tiles,         &n_tiles, &slots, &ctl,       &flags,     &guard,

@@ -7,9 +7,12 @@
 
 #include "lamb_kernels.hip"
 
-// The launchers at the end of the kernel source are not called here.
-hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) {
-    return hipErrorNotSupported;
+// The poll limit that launch_single_pass hands to its kernel; nothing else of a
+// launch is looked at here.
+static uint32_t launched_limit = 0;
+hipError_t hipLaunchKernel(const void *, dim3, dim3, void **arguments, size_t, hipStream_t) {
+    launched_limit = static_cast<const lamb_mi355x::StepArgs *>(arguments[7])->spin_limit;
+    return hipSuccess;
 }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *, const void *, int, size_t) {
     return hipErrorNotSupported;
@@ -151,7 +154,16 @@ uint64_t sleeps_of_a_wait(bool quick, bool one_round, uint32_t index, uint32_t l
     std::vector<uint64_t> slots(6 * tiles.size(), kEmptySlot);
     std::vector<uint32_t> ctl(64, 0), flags(64, 0);
     std::vector<double> ratios(2, -1.0);
-    Call c{&tiles, slots.data(), ctl.data(), flags.data(), ratios.data(), quick, limit};
+    StepArgs args{};
+    args.spin_limit = limit;
+    // (a plan of more than kQuickRounds rounds of one workgroup, for fused_kernel)
+    const int32_t n_tiles = quick ? int32_t(tiles.size()) : 1000;
+    if (launch_single_pass(StepKind{}, 8, tiles.data(), n_tiles, 2, slots.data(), ctl.data(),
+                           flags.data(), false, nullptr, args, FinalizeArgs{}, nullptr, nullptr,
+                           nullptr, nullptr, nullptr, nullptr) != hipSuccess)
+        return 0;
+    Call c{&tiles,        slots.data(), ctl.data(),     flags.data(),
+           ratios.data(), quick,        launched_limit};
     uint64_t n = 0;
     std::thread([&] {
         emulation::run_workgroup(index, 2, uint32_t(kBlock), false, &kernel_body<kLamb, 8>, &c);
