@@ -112,6 +112,17 @@ def counter_traffic(kernel: str, workload: str, src_hash: str):
     return float(t.group(1))
 
 
+QUICK_ROUNDS = 10  # the library's kQuickRounds: plans of more rounds take fused_kernel
+
+
+def single_pass_kernel(single_elems, n_cus: int, tile_groups: int) -> str:
+    """The kernel that takes a plan's single pass, from its number of rounds;
+    ``single_elems``: the elements of each layer on the single pass."""
+    from paper_1904_00962_amd import _lib
+    entries, _, _, _, _, width, _ = _lib.lamb_tile_schedule(single_elems, 4 * n_cus, tile_groups)
+    return "quick_kernel" if len(entries) <= QUICK_ROUNDS * width else "fused_kernel"
+
+
 def copy_probe(args) -> None:
     """A plain device-to-device copy of known size: FETCH_SIZE / WRITE_SIZE of
     this kernel calibrate the counters (bytes per counted KiB)."""
@@ -466,8 +477,10 @@ def main() -> int:
     g_name = "bf16" if g_bytes == 2 else "f32"
     # the roofline entry covers the kernel that takes the most time
     if avg_one >= avg_mom:
-        dom = dict(kernel="fused_kernel<%s, %s, %s, %d groups>" % (algo_name, g_name, args.norm,
-                                                                  tile_groups),
+        cus = torch.cuda.get_device_properties(0).multi_processor_count
+        dom = dict(kernel="%s<%s, %s, %s, %d groups>" % (
+                       single_pass_kernel(single_elems, cus, tile_groups), algo_name, g_name,
+                       args.norm, tile_groups),
                    achieved=one_gbps, bytes_per_launch=b_one * P_single,
                    traffic=counter_traffic("single_pass", workload, src_hash)
                    if default_mode else None)

@@ -1,9 +1,10 @@
 """bench.py on the CPU: its byte model per parameter (the table of
-algorithmic bytes each kernel moves), the single-GPU refusal, and the rule
-that counter traffic from a committed profile is used only while the kernel
+algorithmic bytes each kernel moves), the single-GPU refusal, which of the
+single-pass kernels it names, and the rule that counter traffic from a committed profile is used only while the kernel
 source it was measured on is unchanged."""
 
 import os
+import re
 import subprocess
 import sys
 
@@ -12,6 +13,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 import bench  # noqa: E402
+from paper_1904_00962_amd import build, paramsets  # noqa: E402
 
 
 @pytest.mark.parametrize("algo,g_bytes,deferred,want", [
@@ -54,6 +56,20 @@ def test_more_than_one_gpu_is_refused():
     assert r.returncode != 0
     assert "one GPU" in r.stdout + r.stderr
     assert r.stdout.strip() == "" or not r.stdout.strip().startswith("{")
+
+
+def test_the_single_pass_kernel_is_named_by_the_launcher_s_rule():
+    header = open(os.path.join(build.CSRC, "lamb_internal.h")).read()
+    rounds = int(re.search(r"constexpr int32_t kQuickRounds = (\d+);", header).group(1))
+    assert bench.QUICK_ROUNDS == rounds
+    sizes = lambda specs: [s.numel for s in specs]  # noqa: E731
+    for specs, want in ((paramsets.tiny_tensors(), "quick_kernel"),
+                        (paramsets.resnet50_tensors(), "quick_kernel"),
+                        (paramsets.bert_tensors(1024, 4096, 24, 30522), "fused_kernel")):
+        assert bench.single_pass_kernel(sizes(specs), 256, 8) == want
+    # one round more than the line
+    assert bench.single_pass_kernel([8192] * 1024 * rounds, 256, 8) == "quick_kernel"
+    assert bench.single_pass_kernel([8192] * (1024 * rounds + 1), 256, 8) == "fused_kernel"
 
 
 def test_counter_traffic_only_for_the_profiled_kernel(tmp_path, monkeypatch):
