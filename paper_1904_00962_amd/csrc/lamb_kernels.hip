@@ -1192,6 +1192,47 @@ __device__ __forceinline__ void write_tail(const TileDesc &d, int tail, float s,
     }
 }
 
+// What both kernels read of the plan's state before any of their work.
+__device__ __forceinline__ void start_step(const uint32_t *ctl, const uint32_t *flags,
+                                           int32_t guarded, uint32_t &epoch, uint32_t &fault,
+                                           uint32_t &skip) {
+    epoch = ctl_load(ctl + kCtlEpoch);
+    fault = ctl_load(ctl + kCtlFault);
+    // skip_nonfinite step: the finiteness check's verdict
+    skip = guarded ? flags[kVerdictWord + (epoch & 1u)] : 0u;
+}
+
+// The end of both kernels, for every thread of a workgroup (`skip` is read by
+// the one that needs it).
+__device__ __forceinline__ void finish_step(uint32_t *ctl, uint32_t *flags, int32_t guarded,
+                                            int32_t *nonfinite_out, const uint32_t &skip,
+                                            uint32_t epoch) {
+    // The last workgroup to finish advances the epoch. Every workgroup read
+    // the epoch before any of its work, so none can still be reading it.
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t done =
+            __hip_atomic_fetch_add(ctl + kCtlDone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (done == gridDim.x - 1) {
+            if (guarded && nonfinite_out)
+                *nonfinite_out = skip ? 1 : 0;
+            __hip_atomic_store(ctl + kCtlDone, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (skip) {
+                // A skipped step touched no slot, so its buffer is still empty
+                // and the next step reuses it: the epoch stays, and the raised
+                // verdict word is cleared for that step.
+                flags[kVerdictWord + (epoch & 1u)] = 0u;
+            } else {
+                // Clear the verdict word of the next epoch (last used two
+                // steps ago, read by nothing now) and advance the epoch.
+                flags[kVerdictWord + ((epoch + 1u) & 1u)] = 0u;
+                __hip_atomic_store(ctl + kCtlEpoch, epoch + 1u, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+}
+
 // A leader's gather: this thread's share (slots threadIdx.x, + kBlock, ...) of
 // the layer's `team` partial norms from slot `first` on, combined in that
 // order into (ax, au). False when the wait was abandoned. `eager` loads four
@@ -1275,12 +1316,8 @@ void fused_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
     constexpr int kInRegs = kGroups - kInLds;
     __shared__ f32x4 sh_x[kInLds][kBlock];
     __shared__ TailElems sh_tail[2];
-    if (threadIdx.x == 0) {
-        sh_epoch = ctl_load(ctl + kCtlEpoch);
-        sh_fault = ctl_load(ctl + kCtlFault);
-        // skip_nonfinite step: the finiteness check's verdict
-        sh_skip = guarded ? flags[kVerdictWord + (sh_epoch & 1u)] : 0u;
-    }
+    if (threadIdx.x == 0)
+        start_step(ctl, flags, guarded, sh_epoch, sh_fault, sh_skip);
     __syncthreads();
     const uint32_t epoch = sh_epoch;
     const size_t n = static_cast<size_t>(n_tiles);
@@ -1552,30 +1589,7 @@ void fused_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
         }
     }
 
-    // The last workgroup to finish advances the epoch. Every workgroup read
-    // the epoch before any of its work, so none can still be reading it.
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t done =
-            __hip_atomic_fetch_add(ctl + kCtlDone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (done == gridDim.x - 1) {
-            if (guarded && nonfinite_out)
-                *nonfinite_out = sh_skip ? 1 : 0;
-            __hip_atomic_store(ctl + kCtlDone, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (sh_skip) {
-                // A skipped step touched no slot, so its buffer is still empty
-                // and the next step reuses it: the epoch stays, and the raised
-                // verdict word is cleared for that step.
-                flags[kVerdictWord + (epoch & 1u)] = 0u;
-            } else {
-                // Clear the verdict word of the next epoch (last used two
-                // steps ago, read by nothing now) and advance the epoch.
-                flags[kVerdictWord + ((epoch + 1u) & 1u)] = 0u;
-                __hip_atomic_store(ctl + kCtlEpoch, epoch + 1u, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-    }
+    finish_step(ctl, flags, guarded, nonfinite_out, sh_skip, epoch);
 }
 
 // The single pass of plans of at most kQuickRounds rounds.
@@ -1620,10 +1634,7 @@ void quick_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
     };
     prefetch(d);
     if (threadIdx.x == 0) {
-        sh_epoch = ctl_load(ctl + kCtlEpoch);
-        sh_fault = ctl_load(ctl + kCtlFault);
-        // skip_nonfinite step: the finiteness check's verdict
-        sh_skip = guarded ? flags[kVerdictWord + (sh_epoch & 1u)] : 0u;
+        start_step(ctl, flags, guarded, sh_epoch, sh_fault, sh_skip);
         sh_stop = 0u;
     }
     __syncthreads();
@@ -1787,30 +1798,7 @@ void quick_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
         d = dn;
     }
 
-    // The last workgroup to finish advances the epoch. Every workgroup read
-    // the epoch before any of its work, so none can still be reading it.
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t done =
-            __hip_atomic_fetch_add(ctl + kCtlDone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (done == gridDim.x - 1) {
-            if (guarded && nonfinite_out)
-                *nonfinite_out = sh_skip ? 1 : 0;
-            __hip_atomic_store(ctl + kCtlDone, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (sh_skip) {
-                // A skipped step touched no slot, so its buffer is still empty
-                // and the next step reuses it: the epoch stays, and the raised
-                // verdict word is cleared for that step.
-                flags[kVerdictWord + (epoch & 1u)] = 0u;
-            } else {
-                // Clear the verdict word of the next epoch (last used two
-                // steps ago, read by nothing now) and advance the epoch.
-                flags[kVerdictWord + ((epoch + 1u) & 1u)] = 0u;
-                __hip_atomic_store(ctl + kCtlEpoch, epoch + 1u, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-    }
+    finish_step(ctl, flags, guarded, nonfinite_out, sh_skip, epoch);
 }
 
 // Every tile's x_copy, when a caller attaches or detaches its copies: 24 bytes
