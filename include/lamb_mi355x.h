@@ -461,7 +461,7 @@ LAMB_API lamb_status lamb_plan_u_partials(lamb_plan *plan, void *stream, int32_t
  * flags in a fixed device array of the library: 10.8 MiB, one per device,
  * held from the library's load on that device until the process ends. A call
  * allocates no device or host memory and copies nothing from the host: the
- * tensor table reaches the device as kernel arguments of ceil(n_tensors / 48)
+ * tensor table reaches the device as kernel arguments of ceil(n_tensors / 82)
  * small table kernels, which also clear the array's flag words.
  *   tensors       host array of n_tensors blocks, as lamb_plan_create (v may
  *                 be NULL for LARS); validated on every call

@@ -79,9 +79,10 @@ struct TensorDesc {
     int32_t first_chunk;   // its first fine chunk
     int32_t first_coarse;  // its first coarse chunk
     int32_t out_index;     // the layer's index in ratio_out / norms_out
-    // Padding: with a stride of 64 or 72 bytes the two-pass BERT-Base step was
-    // 0.5% slower (702.3 -> 705.6 us), with 128 bytes the split step of
-    // BERT-Large's 1/8 share 0.9% (255.3 -> 257.7 us).
+    // Padding, of no use that measures: with a stride of 64 bytes the two-pass
+    // step took 0.4% longer on BERT-Base and 0.5% less on ResNet-50, BERT-Large
+    // and its 1/8 share were even (six pairs of processes; where a process's
+    // buffers land alone moves these steps by 1%).
     int32_t reserved[6];
 };
 static_assert(sizeof(TensorDesc) == 88, "TensorDesc layout");

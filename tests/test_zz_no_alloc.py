@@ -90,7 +90,7 @@ def _hp(algo, ps, t, **extra):
 
 
 def test_static_step_equals_the_two_pass_plan_on_calls_in_a_row():
-    # first call: BERT-Base (199 tensors, 5 table batches, 427,665 chunks),
+    # first call: BERT-Base (199 tensors, 3 table batches, 427,665 chunks),
     # two steps; then the smaller tiny set with other algorithms and modes
     big = Twin(1, "lamb")
     try:
