@@ -1595,10 +1595,12 @@ void fused_kernel(const TileDesc *__restrict__ tiles, int32_t n_tiles,
 // The single pass of plans of at most kQuickRounds rounds.
 //
 // Bound by latency: a tile is a chain of descriptor, loads, reduction, a round
-// trip through the layer's leader, stores. Against fused_kernel as it was:
-// the tiny set (0.6M parameters, one round) 15.9 -> 12.4 us a step, sixteen
-// ragged tensors 15.1 -> 11.4 us, ResNet-50 139.5 -> 134.0 us and its LARS step
-// 104.6 -> 98.7 us, BERT-Large's 1/8 share 205.7 -> 199.8 us. In a plan of one
+// trip through the layer's leader, stores. A step (lamb_step_ex), against
+// fused_kernel before there was this one, medians of six pairs of processes:
+// the tiny set (0.6M parameters, one round) 13.3 (12.8 to 15.0) -> 11.6 us,
+// sixteen ragged tensors 15.1 -> 11.6, ten layers of 100,000 elements 19.5 ->
+// 13.2, ResNet-50 139.6 -> 134.3; ResNet-50's LARS step 105.1 -> 98.6 us,
+// BERT-Large's 1/8 share 205.7 -> 199.8. In a plan of one
 // round nothing else fills the wait, and its scale is awaited eagerly (1-2% of
 // such steps; 0.5-1% slower on plans of several rounds).
 template <int kAlgo, bool kBf16, int kNorm, int kGroups>
