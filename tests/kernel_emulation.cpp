@@ -181,7 +181,8 @@ int check_patience() {
     auto expect = [&](const char *what, uint64_t got, uint64_t polls) {
         if (got != polls - 1) {  // (a poll that finds the limit reached does not sleep)
             printf("%s gives up after %llu polls, not %llu\n", what,
-                   static_cast<unsigned long long>(got + 1), static_cast<unsigned long long>(polls));
+                   static_cast<unsigned long long>(got + 1),
+                   static_cast<unsigned long long>(polls));
             ++bad;
         }
     };

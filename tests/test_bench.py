@@ -1,7 +1,8 @@
 """bench.py on the CPU: its byte model per parameter (the table of
 algorithmic bytes each kernel moves), the single-GPU refusal, which of the
-single-pass kernels it names, and the rule that counter traffic from a committed profile is used only while the kernel
-source it was measured on is unchanged."""
+single-pass kernels it names, and the rule that counter traffic from a
+committed profile is used only while the kernel source it was measured on is
+unchanged."""
 
 import os
 import re
